@@ -5,16 +5,13 @@
 // of the [row][n] arrays coalesce across the wavefront:
 //   nodes_kernel  one lane per candidate: lists the prefill and decode nodes (replicas in
 //                 ascending group id, or GPUs in ascending id at per-GPU granularity) with
-//                 their source, node and sink capacities (Appendix A), and, for the listed KV
-//                 path, which replica nodes have a strategy (FlowNet::feas);
+//                 their source, node and sink capacities (Appendix A);
 //   kv_kernel     one lane per (KV edge, candidate): the edge capacity between prefill node
 //                 i and decode node j (connection type 3; Table 1 last row; Appendix A) of
 //                 replica nodes, with the stage-order search of Appendix A (kv_order_kernel)
 //                 when HX_VARIANT_KV_ORDER is set, and the class mix with request classes;
-//   kv_rows_kernel, kv_scan_kernel, kv_compact_kernel, kv_walk_group_kernel  the same edges as
-//                 kv_kernel when hx_score_batch hands over scratch for an edge list: one lane per
-//                 candidate writes every edge with an infeasible end (0, row by row) and lists
-//                 the others, the lists are packed, then 4 lanes per listed edge walk it;
+//   net_kernel    hx_score_batch, replica networks of up to 32 slots: the node rows, the KV edges
+//                 and the flow values that have a closed form, a workgroup per 16 to 64 candidates;
 //   kv_gpu_kernel the same for per-GPU nodes, a workgroup per 64 candidates.
 // hx_score_batch's per-GPU path (up to 128 GPUs and 128 slots) replaces the last two: a table of
 // every link's capacity (link_table_kernel), and nodes_gpu_kernel<W, true>, which settles each
@@ -59,9 +56,8 @@ __global__ void __launch_bounds__(kNodeBlock) nodes_kernel(Problem p, CostOut o,
         // Group slots in chunks of 8: the chunk's loads are issued together, then its slots
         // are appended to the node lists in ascending order.
         constexpr int kC = 8;
-        uint32_t pf = 0, df = 0;  // nodes whose replica has a strategy (tp > 0), by node index
         for (int k0 = 0; k0 < p.Kmax; k0 += kC) {
-            int sz[kC], rl[kC], tq[kC];
+            int sz[kC], rl[kC];
             int32_t cp[kC];
             // every load issued (slots past Kmax read slot Kmax - 1 and are replaced), so that
             // the chunk's loads are in flight together
@@ -71,7 +67,6 @@ __global__ void __launch_bounds__(kNodeBlock) nodes_kernel(Problem p, CostOut o,
                 sz[x] = mask_size<W>(o.members, k, N, n);
                 rl[x] = p.role[(int64_t)k * N + n];
                 cp[x] = o.cap[(int64_t)k * N + n];
-                tq[x] = o.tp[(int64_t)k * N + n];
             }
 #pragma unroll
             for (int x = 0; x < kC; ++x)
@@ -89,19 +84,16 @@ __global__ void __launch_bounds__(kNodeBlock) nodes_kernel(Problem p, CostOut o,
                     f.p_slot[e] = k;
                     f.src_cap[e] = p.coord_cap;
                     f.p_cap[e] = cp[x];
-                    if (tq[x] > 0 && np < 32) pf |= 1u << np;
                     ++np;
                 } else if (rl[x] == HX_DECODE) {
                     const int64_t e = (int64_t)nd * N + n;
                     f.d_slot[e] = k;
                     f.d_cap[e] = cp[x];
                     f.sink_cap[e] = p.coord_cap;
-                    if (tq[x] > 0 && nd < 32) df |= 1u << nd;
                     ++nd;
                 }
             }
         }
-        if (f.feas) f.feas[n] = (uint64_t)pf | ((uint64_t)df << 32);
     } else {
         // Per-GPU nodes: the k-th member (by GPU id) of a replica of sz GPUs and capacity C
         // carries floor(C/sz) + [k < C mod sz].
@@ -1068,60 +1060,6 @@ __global__ void __launch_bounds__(kKvBlock) kv_kernel(Problem p, CostOut o, Flow
                                                            stride);
 }
 
-// The listed KV path, first kernel: a wavefront per piece (64 candidates, blockIdx.y the slice
-// of their KV rows), a lane per candidate walking its rows of the slice below n_p n_d in order
-// (row e of every lane at once, so the stores coalesce): 0 for an edge with an infeasible end
-// (FlowNet::feas), the others listed in the piece's own part of the list (no atomics: a counter
-// that every wavefront bumps serialises them).
-constexpr int kRowsBlock = 256;
-
-__global__ void __launch_bounds__(kRowsBlock) kv_rows_kernel(FlowNet f) {
-    const int64_t N = f.N;
-    const int64_t n0 = (int64_t)blockIdx.x * kRowsBlock + threadIdx.x;
-    const int64_t seg = n0 >> 6;
-    if (seg * 64 >= N) return;  // a wavefront wholly past N owns no piece
-    const bool in = n0 < N;
-    const int64_t n = in ? n0 : N - 1;  // every lane loads, lanes past N own no row
-    const int np = f.n_p[n], nd = f.n_d[n];
-    const uint64_t fz = f.feas[n];
-    const int lane = threadIdx.x & 63;
-    const int r0 = (int)blockIdx.y * f.kv_rows;
-    const int pd = in ? np * nd : 0;
-    const int hi = pd < r0 + f.kv_rows ? pd : r0 + f.kv_rows;  // this lane's rows: [r0, hi)
-    int rows = hi;
-    for (int off = 32; off > 0; off >>= 1) {
-        const int o2 = __shfl_xor(rows, off, 64);
-        rows = o2 > rows ? o2 : rows;
-    }
-    const int64_t piece = seg * kKvSlices + blockIdx.y;
-    uint32_t* list = f.kv_list + piece * (int64_t)(64 * f.kv_rows);
-    int i = 0, j = 0;
-    if (r0 < hi) {
-        i = r0 / nd;
-        j = r0 - i * nd;
-    }
-    const uint32_t dm = (uint32_t)(fz >> 32);
-    // The row advance is formed with selects (i <= n_p <= 32, so the shift stays below 64), so
-    // that only the two stores are predicated.
-    int cnt = 0;
-    int32_t* row = f.kv_cap + (int64_t)r0 * N + n;
-    for (int e = r0; e < rows; ++e, row += N) {
-        const bool live = e < hi;
-        const bool walk = live && ((((uint32_t)(fz >> i) & (dm >> j)) & 1) != 0);
-        if (live && !walk) *row = 0;
-        const uint64_t bal = __ballot(walk);
-        if (bal) {
-            if (walk)
-                list[cnt + __popcll(bal & ((1ull << lane) - 1))] = ((uint32_t)n << 10) | ((uint32_t)i << 5) | (uint32_t)j;
-            cnt += __popcll(bal);
-        }
-        const bool wrap = live && j + 1 == nd;
-        i += wrap ? 1 : 0;
-        j = wrap ? 0 : (live ? j + 1 : j);
-    }
-    if (lane == 0) f.kv_count[piece] = cnt;
-}
-
 // LDS written by some lanes of a wavefront and then read by others of the same wavefront.
 __device__ __forceinline__ void lane_sync() {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -1129,117 +1067,59 @@ __device__ __forceinline__ void lane_sync() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// The listed KV path's packing: one workgroup forms the exclusive prefix sums of the pieces'
-// counts (kv_offs, the total last); each thread takes a contiguous run of pieces (a multiple of
-// four: the piece count is one), sums it, the workgroup scans the 1024 sums, and the thread
-// writes its run's offsets.  A run is read and written in 16-byte words, kScanChunk counts at a
-// time with their loads issued together (the run's last word repeated past its end): one CU
-// does all of it, so the number of memory requests, not bytes, sets the time.
-constexpr int kScanBlock = 1024;
-constexpr int kScanChunk = 16;
-
-__global__ void __launch_bounds__(kScanBlock) kv_scan_kernel(FlowNet f) {
-    __shared__ int32_t part[kScanBlock / 64];
-    constexpr int kWords = kScanChunk / 4;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int64_t P = (f.N + 63) / 64 * kKvSlices;  // a multiple of 4
-    const int64_t run = (P + 4 * kScanBlock - 1) / (4 * kScanBlock) * 4;
-    const int64_t lo = tid * run < P ? tid * run : P, hi = lo + run < P ? lo + run : P;
-    const int4* cw = reinterpret_cast<const int4*>(f.kv_count);
-    int4* ow = reinterpret_cast<int4*>(f.kv_offs);
-    const int64_t wlo = lo / 4, whi = hi / 4;
-    int32_t sum = 0;
-    int4 v0[kWords];  // the last chunk read: the whole run when it fits in one
-    for (int64_t c0 = wlo; c0 < whi; c0 += kWords) {
-#pragma unroll
-        for (int k = 0; k < kWords; ++k) v0[k] = cw[c0 + k < whi ? c0 + k : whi - 1];
-#pragma unroll
-        for (int k = 0; k < kWords; ++k)
-            if (c0 + k < whi) sum += v0[k].x + v0[k].y + v0[k].z + v0[k].w;
-    }
-    int32_t x = sum;  // inclusive scan over the wavefront
-    for (int off = 1; off < 64; off <<= 1) {
-        const int32_t y = __shfl_up(x, off, 64);
-        if (lane >= off) x += y;
-    }
-    if (lane == 63) part[wave] = x;
-    __syncthreads();
-    int32_t before = 0, total = 0;
-    for (int w = 0; w < kScanBlock / 64; ++w) {
-        const int32_t v = part[w];
-        if (w < wave) before += v;
-        total += v;
-    }
-    int32_t off = before + x - sum;
-    if (whi - wlo <= kWords) {  // a run of one chunk: its counts are still in v0
-#pragma unroll
-        for (int k = 0; k < kWords; ++k)
-            if (wlo + k < whi) {
-                int4 o;
-                o.x = off;
-                o.y = o.x + v0[k].x;
-                o.z = o.y + v0[k].y;
-                o.w = o.z + v0[k].z;
-                off = o.w + v0[k].w;
-                ow[wlo + k] = o;
-            }
-    } else
-    for (int64_t c0 = wlo; c0 < whi; c0 += kWords) {
-        int4 v[kWords];
-#pragma unroll
-        for (int k = 0; k < kWords; ++k) v[k] = cw[c0 + k < whi ? c0 + k : whi - 1];
-#pragma unroll
-        for (int k = 0; k < kWords; ++k)
-            if (c0 + k < whi) {
-                int4 o;
-                o.x = off;
-                o.y = o.x + v[k].x;
-                o.z = o.y + v[k].y;
-                o.w = o.z + v[k].z;
-                off = o.w + v[k].w;
-                ow[c0 + k] = o;
-            }
-    }
-    if (tid == 0) f.kv_offs[P] = total;
-}
-
-// Then a wavefront per piece copies its listed edges to kv_flat from its offset on.
-__global__ void __launch_bounds__(256) kv_compact_kernel(FlowNet f) {
-    const int64_t P = (f.N + 63) / 64 * kKvSlices;
-    const int64_t s = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (s >= P) return;
-    const int lane = threadIdx.x & 63;
-    const uint32_t* list = f.kv_list + s * (int64_t)(64 * f.kv_rows);
-    // the part's first 64 entries are loaded with its count and offset (a part has room for
-    // 64 kv_rows >= 64 entries, so the load stays inside it; entries past the count are unused)
-    const uint32_t first = list[lane];
-    const int cnt = f.kv_count[s];
-    const int32_t off = f.kv_offs[s];
-    if (lane < cnt) f.kv_flat[off + lane] = first;
-    for (int x = lane + 64; x < cnt; x += 64) f.kv_flat[off + x] = list[x];
-}
-
-// The listed KV path's walk: kWalkLanes lanes per listed edge.  An edge's links are every
-// overlapping (stage, stage) pair crossed with every overlapping (rank, rank) pair, and the rank
-// pairs (head slices of ptp x dtp) are the same for every stage pair, so lane l of the group
-// takes the rank pairs l, l + kWalkLanes, ... of the merge walk (there are
-// ptp + dtp - gcd(ptp, dtp) <= 15 of them, at most 8 when both degrees are powers of two) and
-// walks the stage pairs (at most ppp + dpp - 1) with them; the group's maximum is the edge's KV
-// time (with kCls one maximum per request class, then sum_k w_k max_k in class order).  Each
-// link's time is the binary64 value kv_time or kv_time_classes forms, and a maximum does not
-// depend on the order.  (The asymmetric split stays with kv_kernel: every lane of a group would
-// recompute the stages' layer counts, which measured twice as slow.)  The group's lanes expand
-// the two member masks together (64 / kWalkLanes bits of each word a lane) into the group's two
-// member columns in LDS.  The edges come from the packed list, kGroups per wavefront at a time,
-// over a grid of kGroupGrid workgroups (about twice what the chip holds at once, so that
-// workgroups that finish early are replaced): the walks run side by side, each starting with a
-// chain of dependent loads (its list entry, slots, then masks and strategies).  Alpha and beta are read from memory: staging them in LDS per workgroup measured
-// slower.
+// The replica networks of hx_score_batch in one kernel (up to 32 group slots, uniform split): a
+// workgroup per 64 candidates lists their nodes, walks their KV edges and settles their flow
+// values, where nodes_kernel, kv_kernel and the max-flow kernel would each read the network back.
+//   nodes   256 / C lanes per candidate take the group slots; a slot's node index is the number of
+//           its side's slots below it, from bit masks met in LDS;
+//   rows    every KV row below n_p n_d is written 0, those lanes taking the rows in turn, then the edges whose two replicas have a strategy are walked and
+//           written over them (a barrier orders the two stores);
+//   walks   kWalkLanes lanes per edge over the workgroup's edges (a candidate has |feasible prefill|
+//           x |feasible decode| of them, found by a search in the prefix sums of these counts).
+//           The rank pairs (head slices of ptp x dtp) are the same for every stage pair, so lane l
+//           takes the rank pairs l, l + kWalkLanes, ... of the merge walk (there are
+//           ptp + dtp - gcd(ptp, dtp) <= 15 of them, at most 8 when both degrees are powers of two)
+//           and walks the stage pairs with them; the group's maximum is the edge's KV time (with
+//           kCls one maximum per request class, then sum_k w_k max_k in class order).  Each link's
+//           time is the binary64 value kv_time or kv_time_classes forms, and a maximum does not
+//           depend on the order;
+//   values  a_i = min(source, node), b_j = min(node, sink).  No a_i > 0 or no b_j > 0: 0.  One such
+//           prefill node: min(a, sum_j min(c_j, b_j)), one decode node likewise (stars; the sums
+//           are LDS atomics of the walk).  Every edge c_ij >= min(a_i, b_j): min(sum a, sum b).  The
+//           others (both sides with several nodes and a thin edge) go to a list that
+//           finish_kernel solves.
+// At 32 GPUs x 65,536 candidates three candidates in four have no flow and all but 181 of the rest
+// are stars, so the value costs a few LDS operations where the max-flow kernel loaded every row of
+// the plan.  Measured against the kernels it replaces (nodes, zero rows and edge list, scan, packing,
+// walks, max-flow: six launches): 32 GPUs x 65,536 64.6 -> 23.9 us, 64 GPUs x 262,144 725 -> 243 us,
+// 8 GPUs x 256 24 -> 8 us.  What bounds it: the walks' binary64 divisions, then the stores of the rows.  (The asymmetric split stays with kv_kernel: every lane of a group would recompute the
+// stages' layer counts, which measured twice as slow.)
 constexpr int kWalkLanes = 4;
-constexpr int kGroupBlock = 256;
-constexpr int kGroupGrid = 4096;
+constexpr int kNetBlock = 256;
+constexpr int kNetWaves = kNetBlock / 64;
+constexpr int kNetMaxK = 32;
 
-__host__ __device__ inline size_t kv_group_lds(int G) { return (size_t)kGroupBlock / kWalkLanes * 2 * G; }
+// LDS of net_kernel before the walk's member columns ([kNetBlock / kWalkLanes] groups of 2 G bytes),
+// C candidates.
+template <int C>
+struct NetShared {
+    int32_t cap[kNetMaxK][C];       // min(coordinator, node) capacity of each slot
+    uint32_t pm[C], dm[C];          // slots with a prefill / decode node
+    uint32_t pf[C], df[C];          // the ones whose replica has a strategy
+    uint32_t pa[C], db[C];          // the ones that can carry flow: a > 0, b > 0
+    int32_t sa[C], sb[C];           // sums of a and b
+    int32_t star_p[C], star_d[C];   // sums over the edges of min(c, b) and of min(c, a)
+    int32_t thin[C];                // some edge below min(a, b)
+    int32_t first[C + 1];           // edges of the candidates before
+};
+template <int C>
+__host__ __device__ inline size_t net_shared_bytes() {
+    return (sizeof(NetShared<C>) + 15) & ~(size_t)15;
+}
+template <int C>
+__host__ __device__ inline size_t net_lds(int G) {
+    return net_shared_bytes<C>() + (size_t)(kNetBlock / kWalkLanes) * 2 * G;
+}
 
 template <int W>
 __device__ __forceinline__ int expand_group(const uint64_t* m, uint8_t* col, int sub) {
@@ -1260,128 +1140,289 @@ __device__ __forceinline__ int expand_group(const uint64_t* m, uint8_t* col, int
     return total;
 }
 
-template <int W, bool kCls>
-__global__ void __launch_bounds__(kGroupBlock) kv_walk_group_kernel(Problem p, CostOut o, FlowNet f) {
-    constexpr int kGroups = 64 / kWalkLanes, kWaves = kGroupBlock / 64;
+// The KV time of an edge whose replicas' members are in colp and cold, by the kWalkLanes lanes of
+// a group (sub: the lane's index in it).  Every lane returns it.
+template <bool kCls>
+__device__ __forceinline__ double walk_edge(const Problem& p, const uint8_t* colp, int ptp, int ppp, const uint8_t* cold,
+                                            int dtp, int dpp, int sub, bool ok) {
     constexpr int kC = kCls ? HX_MAX_CLASSES : 1;
-    static_assert(64 % kWalkLanes == 0 && kWalkLanes <= 64, "lanes of a group split each mask word");
     constexpr int kPairs = (2 * HX_MAX_TP - 1 + kWalkLanes - 1) / kWalkLanes;  // rank pairs a lane
-    extern __shared__ __attribute__((aligned(16))) uint8_t sm[];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int grp = lane / kWalkLanes, sub = lane % kWalkLanes;
-    const int G = p.G;
-    const int64_t N = p.N;
-    uint8_t* colp = sm + (size_t)(wave * kGroups + grp) * 2 * G;  // [G] prefill member ids
-    uint8_t* cold = colp + G;                                     // [G] decode member ids
     const int nc = kCls ? p.n_cls : 1;
-    double V1[kC];
+    const int G = p.G;
+    double V1[kC], worst[kC];
 #pragma unroll
-    for (int k = 0; k < kC; ++k) V1[k] = 2.0 * (kCls ? p.cls_in[k] : p.s_in) * p.Hkv * p.B;
-    const int64_t total = f.kv_offs[(N + 63) / 64 * kKvSlices];
-    for (int64_t w = (int64_t)blockIdx.x * kWaves + wave; w * kGroups < total; w += (int64_t)gridDim.x * kWaves) {
-        const int64_t x = w * kGroups + grp;
-        const bool live = x < total;
-        const uint32_t v = f.kv_flat[live ? x : w * kGroups];
-        const int64_t n = v >> 10;
-        const int i = (v >> 5) & 31, j = v & 31;
-        const int nd = f.n_d[n];
-        const int kp = f.p_slot[(int64_t)i * N + n], kd = f.d_slot[(int64_t)j * N + n];
-        uint64_t mp[W], md[W];
+    for (int k = 0; k < kC; ++k) {
+        V1[k] = 2.0 * (kCls ? p.cls_in[k] : p.s_in) * p.Hkv * p.B;
+        worst[k] = 0.0;
+    }
+    if (ok) {
+        // this lane's rank pairs: steps sub, sub + kWalkLanes, ... of the merge of the two
+        // head partitions (rl < 0: none)
+        int rl[kPairs], ql[kPairs], ovl[kPairs];
 #pragma unroll
-        for (int ww = 0; ww < W; ++ww) {
-            mp[ww] = o.members[((int64_t)kp * W + ww) * N + n];
-            md[ww] = o.members[((int64_t)kd * W + ww) * N + n];
+        for (int h = 0; h < kPairs; ++h) {
+            rl[h] = -1;
+            ql[h] = 0;
+            ovl[h] = 0;
         }
-        const int ptp = o.tp[(int64_t)kp * N + n], ppp = o.pp[(int64_t)kp * N + n];
-        const int dtp = o.tp[(int64_t)kd * N + n], dpp = o.pp[(int64_t)kd * N + n];
-        const int cp = expand_group<W>(mp, colp, sub), cd = expand_group<W>(md, cold, sub);
-        lane_sync();
-        // A strategy whose tp*pp is not the group's size (cost outputs of another batch) is
-        // treated as infeasible rather than read past the member list.
-        const bool ok = live && ptp > 0 && dtp > 0 && cp == ptp * ppp && cd == dtp * dpp;
-        double worst[kC];
+        {
+            int r = 0, q = 0;
+            for (int t = 0; t < kPairs * kWalkLanes && r < ptp && q < dtp; ++t) {
+                const int re = (r + 1) * dtp, qe = (q + 1) * ptp;
+                const int ov = (re < qe ? re : qe) - (r * dtp > q * ptp ? r * dtp : q * ptp);
 #pragma unroll
-        for (int k = 0; k < kC; ++k) worst[k] = 0.0;
-        if (ok) {
-            // this lane's rank pairs: steps sub, sub + kWalkLanes, ... of the merge of the two
-            // head partitions (rl < 0: none)
-            int rl[kPairs], ql[kPairs], ovl[kPairs];
+                for (int h = 0; h < kPairs; ++h)
+                    if (t == sub + h * kWalkLanes) {
+                        rl[h] = r;
+                        ql[h] = q;
+                        ovl[h] = ov;
+                    }
+                if (re <= qe) ++r;
+                if (qe <= re) ++q;
+            }
+        }
+        const int deni = ptp * dtp;
+        const double den = (double)deni;
+        const bool pow2 = (deni & (deni - 1)) == 0;
+        const double inv_den = 1.0 / den;
+        const int lqp = p.L / ppp, lrp = p.L % ppp, lqd = p.L / dpp, lrd = p.L % dpp;
+        int a = 0, bb = 0, a0 = 0, b0 = 0;
+        int a1 = lqp + (0 < lrp ? 1 : 0), b1 = lqd + (0 < lrd ? 1 : 0);
+        while (a < ppp && bb < dpp) {
+            const int nab = (a1 < b1 ? a1 : b1) - (a0 > b0 ? a0 : b0);
 #pragma unroll
             for (int h = 0; h < kPairs; ++h) {
-                rl[h] = -1;
-                ql[h] = 0;
-                ovl[h] = 0;
-            }
-            {
-                int r = 0, q = 0;
-                for (int t = 0; t < kPairs * kWalkLanes && r < ptp && q < dtp; ++t) {
-                    const int re = (r + 1) * dtp, qe = (q + 1) * ptp;
-                    const int ov = (re < qe ? re : qe) - (r * dtp > q * ptp ? r * dtp : q * ptp);
+                const int rr = rl[h], qq = ql[h], oo = ovl[h];
+                if (rr < 0) continue;
+                const int e = colp[a * ptp + rr] * G + cold[bb * dtp + qq];
+                const double al = p.alpha[e], be = p.beta[e];
 #pragma unroll
-                    for (int h = 0; h < kPairs; ++h)
-                        if (t == sub + h * kWalkLanes) {
-                            rl[h] = r;
-                            ql[h] = q;
-                            ovl[h] = ov;
-                        }
-                    if (re <= qe) ++r;
-                    if (qe <= re) ++q;
+                for (int k = 0; k < kC; ++k) {
+                    if (k >= nc) break;
+                    const double Vn = V1[k] * (double)nab;
+                    const double bytes = pow2 ? (Vn * (double)oo) * inv_den : (Vn * (double)oo) / den;
+                    const double time = al + bytes / be;
+                    if (time > worst[k]) worst[k] = time;
                 }
             }
-            const int deni = ptp * dtp;
-            const double den = (double)deni;
-            const bool pow2 = (deni & (deni - 1)) == 0;
-            const double inv_den = 1.0 / den;
-            const int lqp = p.L / ppp, lrp = p.L % ppp, lqd = p.L / dpp, lrd = p.L % dpp;
-            int a = 0, bb = 0, a0 = 0, b0 = 0;
-            int a1 = lqp + (0 < lrp ? 1 : 0), b1 = lqd + (0 < lrd ? 1 : 0);
-            while (a < ppp && bb < dpp) {
-                const int nab = (a1 < b1 ? a1 : b1) - (a0 > b0 ? a0 : b0);
-#pragma unroll
-                for (int h = 0; h < kPairs; ++h) {
-                    const int rr = rl[h], qq = ql[h], oo = ovl[h];
-                    if (rr < 0) continue;
-                    const int e = colp[a * ptp + rr] * G + cold[bb * dtp + qq];
-                    const double al = p.alpha[e], be = p.beta[e];
-#pragma unroll
-                    for (int k = 0; k < kC; ++k) {
-                        if (k >= nc) break;
-                        const double Vn = V1[k] * (double)nab;
-                        const double bytes = pow2 ? (Vn * (double)oo) * inv_den : (Vn * (double)oo) / den;
-                        const double time = al + bytes / be;
-                        if (time > worst[k]) worst[k] = time;
-                    }
-                }
-                const bool adv_a = a1 <= b1, adv_b = b1 <= a1;
-                if (adv_a) {
-                    ++a;
-                    a0 = a1;
-                    a1 = a0 + lqp + (a < lrp ? 1 : 0);
-                }
-                if (adv_b) {
-                    ++bb;
-                    b0 = b1;
-                    b1 = b0 + lqd + (bb < lrd ? 1 : 0);
-                }
+            const bool adv_a = a1 <= b1, adv_b = b1 <= a1;
+            if (adv_a) {
+                ++a;
+                a0 = a1;
+                a1 = a0 + lqp + (a < lrp ? 1 : 0);
+            }
+            if (adv_b) {
+                ++bb;
+                b0 = b1;
+                b1 = b0 + lqd + (bb < lrd ? 1 : 0);
             }
         }
+    }
 #pragma unroll
-        for (int k = 0; k < kC; ++k)
+    for (int k = 0; k < kC; ++k)
 #pragma unroll
-            for (int off = kWalkLanes / 2; off > 0; off >>= 1) {
-                const double w2 = __shfl_xor(worst[k], off, 64);
-                worst[k] = w2 > worst[k] ? w2 : worst[k];
-            }
-        double t = worst[0];
-        if (kCls) {
-            t = 0.0;
-#pragma unroll
-            for (int k = 0; k < kC; ++k)
-                if (k < nc) t = t + p.cls_w[k] * worst[k];
+        for (int off = kWalkLanes / 2; off > 0; off >>= 1) {
+            const double w2 = __shfl_xor(worst[k], off, 64);
+            worst[k] = w2 > worst[k] ? w2 : worst[k];
         }
-        if (live && sub == 0) f.kv_cap[(int64_t)(i * nd + j) * N + n] = ok ? quantize(1000.0 / t) : 0;
+    if (!kCls) return worst[0];
+    double t = 0.0;
+#pragma unroll
+    for (int k = 0; k < kC; ++k)
+        if (k < nc) t = t + p.cls_w[k] * worst[k];
+    return t;
+}
+
+// The i-th set bit of m (i below its bit count).
+__device__ __forceinline__ int nth_bit(uint32_t m, int i) {
+    for (; i > 0; --i) m &= m - 1;
+    return __ffs(m) - 1;
+}
+
+template <int W, bool kCls, int C>
+__global__ void __launch_bounds__(kNetBlock) net_kernel(Problem p, CostOut o, FlowNet f, int32_t* flow_value,
+                                                        unsigned long long* arg, int32_t* list_count, int32_t* list) {
+    static_assert(64 % C == 0 && C >= kNetWaves, "a wavefront holds whole sets of candidates");
+    constexpr int kGroups = 64 / kWalkLanes;
+    constexpr int kParts = kNetBlock / C;                              // lanes that share a candidate's slots and rows
+    constexpr int kSlots = (kNetMaxK + kParts - 1) / kParts;           // slots a lane takes, at most
+    extern __shared__ __attribute__((aligned(16))) uint8_t sm[];
+    NetShared<C>& S = *reinterpret_cast<NetShared<C>*>(sm);
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int ci = tid % C, part = tid / C;
+    const int G = p.G, Kmax = p.Kmax;
+    const int64_t N = p.N;
+    // workgroups are dealt to the 8 XCDs in turn: each XCD takes a contiguous range of candidates,
+    // so that the rows' cache lines (64 candidates are half a line of the byte rows) stay in its L2
+    const int tiles = (int)((N + C - 1) / C), chunk = (tiles + 7) / 8;
+    const int tile = (int)(blockIdx.x & 7) * chunk + (int)(blockIdx.x >> 3);
+    if ((int)(blockIdx.x >> 3) >= chunk || tile >= tiles) return;  // uniform
+    const int64_t n0 = (int64_t)tile * C, n = n0 + ci;
+    const bool in = n < N;
+    const int64_t nl = in ? n : N - 1;  // every lane loads; lanes past N own nothing
+    if (tid < C) {
+        S.pm[ci] = S.dm[ci] = S.pf[ci] = S.df[ci] = S.pa[ci] = S.db[ci] = 0;
+        S.sa[ci] = S.sb[ci] = S.star_p[ci] = S.star_d[ci] = S.thin[ci] = 0;
+    }
+
+    // nodes: this lane's slots [k0, k0 + per), every load issued together (slots past the range
+    // read its last slot and are dropped)
+    const int per = (Kmax + kParts - 1) / kParts, k0 = part * per;
+    int32_t cp[kSlots];
+    int sz[kSlots], rl[kSlots], tq[kSlots];
+#pragma unroll
+    for (int x = 0; x < kSlots; ++x) {
+        const int k = k0 + x < Kmax ? k0 + x : Kmax - 1;
+        sz[x] = mask_size<W>(o.members, k, N, (int)nl);
+        rl[x] = p.role[(int64_t)k * N + nl];
+        cp[x] = o.cap[(int64_t)k * N + nl];
+        tq[x] = o.tp[(int64_t)k * N + nl];
+    }
+    __syncthreads();  // S cleared
+    {
+        uint32_t pm = 0, dm = 0, pf = 0, df = 0, pa = 0, db = 0;
+        int32_t sa = 0, sb = 0;
+#pragma unroll
+        for (int x = 0; x < kSlots; ++x) {
+            const int k = k0 + x;
+            if (x >= per || k >= Kmax || !in || sz[x] == 0) continue;
+            const int32_t c = cp[x] < p.coord_cap ? cp[x] : p.coord_cap;
+            const uint32_t bit = 1u << k;
+            S.cap[k][ci] = c;
+            if (rl[x] == HX_PREFILL) {
+                pm |= bit;
+                if (tq[x] > 0) pf |= bit;
+                if (c > 0) pa |= bit;
+                sa += c;
+            } else if (rl[x] == HX_DECODE) {
+                dm |= bit;
+                if (tq[x] > 0) df |= bit;
+                if (c > 0) db |= bit;
+                sb += c;
+            }
+        }
+        if (pm) atomicOr(&S.pm[ci], pm);
+        if (dm) atomicOr(&S.dm[ci], dm);
+        if (pf) atomicOr(&S.pf[ci], pf);
+        if (df) atomicOr(&S.df[ci], df);
+        if (pa) atomicOr(&S.pa[ci], pa);
+        if (db) atomicOr(&S.db[ci], db);
+        if (sa) atomicAdd(&S.sa[ci], sa);
+        if (sb) atomicAdd(&S.sb[ci], sb);
+    }
+    __builtin_amdgcn_s_waitcnt(0xC07F);  // the LDS atomics have landed (lgkmcnt(0))
+    __syncthreads();
+    const uint32_t pm = S.pm[ci], dm = S.dm[ci];
+    const int np = __popc(pm), nd = __popc(dm);
+#pragma unroll
+    for (int x = 0; x < kSlots; ++x) {
+        const int k = k0 + x;
+        if (x >= per || k >= Kmax) break;
+        const uint32_t below = (1u << k) - 1;
+        if ((pm >> k) & 1) {
+            const int64_t e = (int64_t)__popc(pm & below) * N + n;
+            f.p_slot[e] = k;
+            f.src_cap[e] = p.coord_cap;
+            f.p_cap[e] = cp[x];
+        } else if ((dm >> k) & 1) {
+            const int64_t e = (int64_t)__popc(dm & below) * N + n;
+            f.d_slot[e] = k;
+            f.d_cap[e] = cp[x];
+            f.sink_cap[e] = p.coord_cap;
+        }
+    }
+    // KV rows: zeros, this lane every kParts-th row
+    const int pd = np * nd;
+    {
+        int32_t* row = f.kv_cap + (int64_t)part * N + n;
+        for (int e = part; e < pd; e += kParts, row += kParts * N) *row = 0;
+    }
+    // the edges to walk, by candidate
+    if (wave == 0) {
+        const int ec = lane < C ? __popc(S.pf[ci]) * __popc(S.df[ci]) : 0;
+        int incl = ec;
+        for (int off = 1; off < C; off <<= 1) {
+            const int v = __shfl_up(incl, off, 64);
+            if (lane >= off) incl += v;
+        }
+        if (lane < C) S.first[lane + 1] = incl;
+        if (lane == 0) S.first[0] = 0;
+        if (lane < C && in) {
+            f.n_p[n] = np;
+            f.n_d[n] = nd;
+        }
+    }
+    __syncthreads();
+
+    const int edges = S.first[C];
+    uint8_t* colp = sm + net_shared_bytes<C>() +
+                    (size_t)(wave * kGroups + lane / kWalkLanes) * 2 * G;  // [G] prefill member ids
+    uint8_t* cold = colp + G;                                             // [G] decode member ids
+    const int sub = lane % kWalkLanes;
+    for (int base = wave * kGroups; base < edges; base += kNetWaves * kGroups) {
+        const int x = base + lane / kWalkLanes;
+        const bool live = x < edges;
+        const int xe = live ? x : base;
+        int c = 0;  // the last candidate whose edges start at or before xe
+#pragma unroll
+        for (int step = C / 2; step > 0; step >>= 1)
+            if (S.first[c + step] <= xe) c += step;
+        const int64_t m = n0 + c;
+        const int r = xe - S.first[c];
+        const uint32_t cpf = S.pf[c], cdf = S.df[c];
+        const int q = __popc(cdf), i = r / q;
+        const int kp = nth_bit(cpf, i), kd = nth_bit(cdf, r - i * q);
+        uint64_t mp[W], md[W];
+#pragma unroll
+        for (int w = 0; w < W; ++w) {
+            mp[w] = o.members[((int64_t)kp * W + w) * N + m];
+            md[w] = o.members[((int64_t)kd * W + w) * N + m];
+        }
+        const int ptp = o.tp[(int64_t)kp * N + m], ppp = o.pp[(int64_t)kp * N + m];
+        const int dtp = o.tp[(int64_t)kd * N + m], dpp = o.pp[(int64_t)kd * N + m];
+        const int np_m = expand_group<W>(mp, colp, sub), nd_m = expand_group<W>(md, cold, sub);
+        lane_sync();
+        // A strategy whose tp*pp is not the group's size is treated as infeasible rather than read
+        // past the member list.
+        const bool ok = live && ptp > 0 && dtp > 0 && np_m == ptp * ppp && nd_m == dtp * dpp;
+        const double t = walk_edge<kCls>(p, colp, ptp, ppp, cold, dtp, dpp, sub, ok);
+        if (live && sub == 0) {
+            const int32_t v = ok ? quantize(1000.0 / t) : 0;
+            const int ei = __popc(S.pm[c] & ((1u << kp) - 1)), ej = __popc(S.dm[c] & ((1u << kd) - 1));
+            f.kv_cap[(int64_t)(ei * __popc(S.dm[c]) + ej) * N + m] = v;
+            const int32_t a = S.cap[kp][c], b = S.cap[kd][c];
+            if (a > 0 && b > 0) {
+                atomicAdd(&S.star_p[c], v < b ? v : b);
+                atomicAdd(&S.star_d[c], v < a ? v : a);
+                if (v < (a < b ? a : b)) S.thin[c] = 1;
+            }
+        }
         lane_sync();  // the next edge's expansion overwrites the columns
     }
+    __builtin_amdgcn_s_waitcnt(0xC07F);
+    __syncthreads();
+    if (wave != 0) return;
+    // values: sums of at most 32 capacities below 2^24
+    const bool own = lane < C && in;
+    const int32_t sa = S.sa[ci], sb = S.sb[ci];
+    const int na = __popc(S.pa[ci]), nb = __popc(S.db[ci]);
+    int32_t v = 0;
+    bool left = false;
+    if (na > 0 && nb > 0) {
+        if (na == 1) v = sa < S.star_p[ci] ? sa : S.star_p[ci];
+        else if (nb == 1) v = sb < S.star_d[ci] ? sb : S.star_d[ci];
+        else if (!S.thin[ci]) v = sa < sb ? sa : sb;
+        else left = true;
+    }
+    if (own && !left) flow_value[n] = v;
+    const uint64_t bal = __ballot(own && left);
+    if (bal) {
+        int32_t at = 0;
+        if (lane == 0) at = atomicAdd(list_count, (int32_t)__popcll(bal));
+        at = __shfl(at, 0, 64);
+        if (own && left) list[at + __popcll(bal & ((1ull << lane) - 1))] = (int32_t)n;
+    }
+    fold_argmax(own && !left ? argmax_key(v, (int32_t)n) : 0ull, arg);
 }
 
 // Per-GPU nodes: one workgroup of kGpuKvWaves wavefronts per 64 candidates (a lane per
@@ -1559,18 +1600,6 @@ hipError_t launch_w(const Problem& p, const CostOut& o, const FlowNet& f, hipStr
         if (e != hipSuccess) return e;
     } else if (p.variant & HX_VARIANT_KV_ORDER) {
         hipLaunchKernelGGL(kv_order_kernel<W>, dim3(blocks), dim3(kOrderThreads), kOrderLds + lds, s, p, o, f);
-    } else if (f.kv_list && !(p.variant & HX_VARIANT_ASYM)) {
-        // the listed path: zero rows and the edge list, its packing, then the walks
-        const int64_t pieces = (p.N + 63) / 64 * kKvSlices;
-        hipLaunchKernelGGL(kv_rows_kernel, dim3((unsigned)((p.N + kRowsBlock - 1) / kRowsBlock), kKvSlices),
-                           dim3(kRowsBlock), 0, s, f);
-        hipLaunchKernelGGL(kv_scan_kernel, dim3(1), dim3(kScanBlock), 0, s, f);
-        hipLaunchKernelGGL(kv_compact_kernel, dim3((unsigned)((pieces + 3) / 4)), dim3(256), 0, s, f);
-        const size_t gl = kv_group_lds(p.G);
-        if (p.n_cls > 0)
-            hipLaunchKernelGGL((kv_walk_group_kernel<W, true>), dim3(kGroupGrid), dim3(kGroupBlock), gl, s, p, o, f);
-        else
-            hipLaunchKernelGGL((kv_walk_group_kernel<W, false>), dim3(kGroupGrid), dim3(kGroupBlock), gl, s, p, o, f);
     } else if (p.variant & HX_VARIANT_ASYM) {
         hipLaunchKernelGGL((kv_kernel<W, true, false>), grid_kv, dim3(kKvBlock), lds + sizeof(double) * p.G, s, p,
                            o, f);
@@ -1612,6 +1641,50 @@ size_t link_table_bytes(int32_t n_gpus, int32_t n_cand) {
 
 int32_t* flownet_values_list_count(void* table, int32_t n_gpus) {
     return reinterpret_cast<int32_t*>(static_cast<unsigned char*>(table) + list_offset(n_gpus));
+}
+
+bool score_net_fits(const Problem& p) {
+    return p.granularity == 0 && p.Kmax <= kNetMaxK && !(p.variant & (HX_VARIANT_ASYM | HX_VARIANT_KV_ORDER));
+}
+
+template <int W, bool kCls, int C>
+static void launch_net_c(const Problem& p, const CostOut& o, const FlowNet& f, int32_t* flow_value,
+                         unsigned long long* slots, int32_t* list_count, int32_t* list, hipStream_t s) {
+    const int64_t tiles = ((int64_t)p.N + C - 1) / C;
+    hipLaunchKernelGGL((net_kernel<W, kCls, C>), dim3((unsigned)(8 * ((tiles + 7) / 8))), dim3(kNetBlock),
+                       net_lds<C>(p.G), s, p, o, f, flow_value, slots, list_count, list);
+}
+
+template <int W, bool kCls>
+static void launch_net(const Problem& p, const CostOut& o, const FlowNet& f, int32_t* flow_value,
+                       unsigned long long* slots, int32_t* list_count, int32_t* list, hipStream_t s) {
+    // Candidates per workgroup: the fewest of 16, 32, 64 that need at most 1,024 workgroups (four
+    // per CU, 16 wavefronts), so that small batches still spread over the chip, and 64 beyond.
+    // Measured: 16 GPUs x 4,096 candidates 9.3 us with 16 against 18.2 with 64; 27 GPUs x 10,007
+    // with many feasible edges 27.6 against 49.7; 32 GPUs x 65,536 43.8 against 23.4 (28.8 with 32).
+    if (p.N <= 16 * 1024)
+        launch_net_c<W, kCls, 16>(p, o, f, flow_value, slots, list_count, list, s);
+    else if (p.N <= 32 * 1024)
+        launch_net_c<W, kCls, 32>(p, o, f, flow_value, slots, list_count, list, s);
+    else
+        launch_net_c<W, kCls, 64>(p, o, f, flow_value, slots, list_count, list, s);
+}
+
+hipError_t launch_score_net(const Problem& p, const CostOut& o, const FlowNet& f, int32_t* flow_value,
+                            unsigned long long* slots, int32_t* list_count, int32_t* list, hipStream_t s) {
+    prof_mark(kKKv, false, s);
+    const int W = mask_words(p.G);
+    if (p.n_cls > 0) {
+        if (W == 1) launch_net<1, true>(p, o, f, flow_value, slots, list_count, list, s);
+        else if (W == 2) launch_net<2, true>(p, o, f, flow_value, slots, list_count, list, s);
+        else launch_net<4, true>(p, o, f, flow_value, slots, list_count, list, s);
+    } else {
+        if (W == 1) launch_net<1, false>(p, o, f, flow_value, slots, list_count, list, s);
+        else if (W == 2) launch_net<2, false>(p, o, f, flow_value, slots, list_count, list, s);
+        else launch_net<4, false>(p, o, f, flow_value, slots, list_count, list, s);
+    }
+    prof_mark(kKKv, true, s);
+    return hipGetLastError();
 }
 
 hipError_t launch_flownet_values(const Problem& p, const CostOut& o, const FlowNet& f, int32_t* flow_value,

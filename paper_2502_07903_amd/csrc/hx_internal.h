@@ -35,60 +35,7 @@ struct CostOut {
 struct FlowNet {
     int32_t N, max_p, max_d, max_pd;
     int32_t *n_p, *n_d, *p_slot, *d_slot, *src_cap, *p_cap, *kv_cap, *d_cap, *sink_cap;
-    // Optional scratch of the listed KV path (replica nodes, kv_list_fits), per piece: 64
-    // candidates (s = n / 64) and a slice r of kKvSlices of their KV rows (rows r kv_rows to
-    // (r + 1) kv_rows - 1):
-    //   feas     [N]: bit i of the low word set when prefill node i's replica has a strategy,
-    //            bit j of the high word the same for decode node j (nodes_kernel writes it);
-    //   kv_count [ceil(N / 64)][kKvSlices]: how many of the piece's KV edges are listed;
-    //   kv_list  [ceil(N / 64)][kKvSlices][64 kv_rows]: the piece's KV edges whose two replicas
-    //            have a strategy, (n << 10) | (i << 5) | j, in row order (kv_rows_kernel writes
-    //            both, kv_walk_kernel walks them).
-    //   kv_offs  [pieces + 1]: exclusive prefix sums of kv_count, the total last;
-    //   kv_flat  the listed edges of all pieces, packed in piece order (kv_offs[s] onwards).
-    uint64_t* feas = nullptr;
-    int32_t* kv_count = nullptr;
-    uint32_t* kv_list = nullptr;
-    int32_t* kv_offs = nullptr;
-    uint32_t* kv_flat = nullptr;
-    int32_t kv_rows = 0;  // ceil(floor(Kmax/2) ceil(Kmax/2) / kKvSlices)
 };
-
-constexpr int kKvSlices = 4;
-
-// The listed KV path takes networks of up to 32 replica slots (node indices in 5 bits, bits of
-// feas) and up to 2^22 candidates (n in the list entry's other 22 bits).
-inline bool kv_list_fits(int32_t granularity, int32_t max_groups, int32_t n_cand) {
-    return granularity == 0 && max_groups <= 32 && n_cand <= (1 << 22);
-}
-// Its scratch: the pieces' counts and offsets, feas, then twice room for every KV row of every
-// piece (the per-piece lists and the packed list).
-inline int32_t kv_slice_rows(int32_t max_groups) {
-    return ((max_groups / 2) * ((max_groups + 1) / 2) + kKvSlices - 1) / kKvSlices;
-}
-inline size_t kv_pieces(int32_t n_cand) { return (size_t)kKvSlices * (((size_t)n_cand + 63) / 64); }
-inline size_t kv_round256(size_t x) { return (x + 255) & ~(size_t)255; }
-inline size_t kv_list_entries(int32_t max_groups, int32_t n_cand) {
-    return kv_pieces(n_cand) * 64 * (size_t)kv_slice_rows(max_groups);
-}
-inline size_t kv_list_bytes(int32_t max_groups, int32_t n_cand) {
-    return kv_round256(sizeof(int32_t) * kv_pieces(n_cand)) + kv_round256(sizeof(int32_t) * (kv_pieces(n_cand) + 1)) +
-           kv_round256(sizeof(uint64_t) * (size_t)n_cand) +
-           2 * kv_round256(sizeof(uint32_t) * kv_list_entries(max_groups, n_cand));
-}
-inline void kv_list_carve(FlowNet& f, void* base, int32_t max_groups, int32_t n_cand) {
-    unsigned char* b = static_cast<unsigned char*>(base);
-    f.kv_count = reinterpret_cast<int32_t*>(b);
-    b += kv_round256(sizeof(int32_t) * kv_pieces(n_cand));
-    f.kv_offs = reinterpret_cast<int32_t*>(b);
-    b += kv_round256(sizeof(int32_t) * (kv_pieces(n_cand) + 1));
-    f.feas = reinterpret_cast<uint64_t*>(b);
-    b += kv_round256(sizeof(uint64_t) * (size_t)n_cand);
-    f.kv_list = reinterpret_cast<uint32_t*>(b);
-    b += kv_round256(sizeof(uint32_t) * kv_list_entries(max_groups, n_cand));
-    f.kv_flat = reinterpret_cast<uint32_t*>(b);
-    f.kv_rows = kv_slice_rows(max_groups);
-}
 
 // Capacity in milli-requests/s: floor(x), clamped to [0, HX_CAP_MAX].
 __device__ __forceinline__ int32_t quantize(double x) {
@@ -169,9 +116,18 @@ hipError_t launch_best(const int32_t* flow_value, int32_t n, int32_t* best, hipS
 size_t best_parts_bytes();
 // The fused argmax: slots of 64-bit keys, ordered as (value, then lower index) so that a larger key
 // is a better candidate; 0 is no candidate (below every value a flow or an error code takes).
-constexpr int kArgSlots = 4096;
+constexpr int kArgSlots = 1024;
 __host__ __device__ inline unsigned long long argmax_key(int32_t value, int32_t n) {
     return ((unsigned long long)((uint32_t)value ^ 0x80000000u) << 32) | (unsigned long long)(0xFFFFFFFFu - (uint32_t)n);
+}
+// Folds the best key of a wavefront's lanes into slot blockIdx mod kArgSlots of arg with a 64-bit
+// atomic max; every lane of the wavefront calls it (key 0: no candidate).
+__device__ __forceinline__ void fold_argmax(unsigned long long key, unsigned long long* arg) {
+    for (int off = 32; off > 0; off >>= 1) {
+        const unsigned long long o = __shfl_xor(key, off, 64);
+        key = o > key ? o : key;
+    }
+    if ((threadIdx.x & 63) == 0 && key != 0) atomicMax(&arg[blockIdx.x % kArgSlots], key);
 }
 hipError_t launch_best_final(const unsigned long long* slots, int32_t* best, hipStream_t s);
 hipError_t launch_best_parts(const int32_t* flow_value, int32_t n, int32_t* best, int32_t* counter, uint64_t* part,
@@ -189,6 +145,16 @@ size_t link_table_bytes(int32_t n_gpus, int32_t n_cand);
 int32_t* flownet_values_list_count(void* table, int32_t n_gpus);
 hipError_t launch_flownet_values(const Problem& p, const CostOut& o, const FlowNet& f, int32_t* flow_value,
                                  void* table, hipStream_t s);
+// hx_score_batch, replica networks of up to 32 group slots (score_net_fits): one kernel writes the
+// node and KV rows and every flow value that a closed form gives, and lists the other candidates
+// (*list_count, zero at launch); launch_finish solves those and reduces the argmax slots (zero at
+// launch) into best.  ticket: a zeroed word.
+bool score_net_fits(const Problem& p);
+hipError_t launch_score_net(const Problem& p, const CostOut& o, const FlowNet& f, int32_t* flow_value,
+                            unsigned long long* slots, int32_t* list_count, int32_t* list, hipStream_t s);
+hipError_t launch_finish(const Problem& p, const FlowNet& f, int32_t* flow_value, int32_t round_budget,
+                         unsigned long long* slots, const int32_t* list_count, const int32_t* list, int32_t* ticket,
+                         int32_t* best, hipStream_t s);
 bool maxflow_workgroup_plan(int32_t max_p, int32_t max_d, int32_t max_pd);
 hipError_t launch_maxflow_listed(const FlowNet& f, int32_t* flow_value, int32_t round_budget, const int32_t* list,
                                  const int32_t* count, hipStream_t s);

@@ -241,30 +241,23 @@ __global__ void __launch_bounds__(64) dom_kernel(FlowNet f, int32_t* flow_value)
 // The work of one tile (64/SEG candidates of a packed plan, or one candidate of a workgroup
 // plan); every lane of the workgroup calls it with the same tile.
 // kArg: fold the best of each wavefront's candidates (lane 0 of a segment holds its candidate's
-// key, argmax_key) into slot blockIdx mod kArgSlots of arg with a 64-bit atomic max; every lane of
-// the wavefront calls it.
-__device__ __forceinline__ void fold_argmax(unsigned long long key, unsigned long long* arg) {
-    for (int off = 32; off > 0; off >>= 1) {
-        const unsigned long long o = __shfl_xor(key, off, 64);
-        key = o > key ? o : key;
-    }
-    if ((threadIdx.x & 63) == 0 && key != 0) atomicMax(&arg[blockIdx.x % kArgSlots], key);
-}
-
+// key, argmax_key) into arg.  list: the tile's candidates are the tile-th kPer of the listed ones.
 template <int SEG, bool kStats, bool kArg = false>
 __device__ __forceinline__ void maxflow_tile(const FlowNet& f, int32_t* flow_value, int32_t* kv_flow, uint8_t* cut,
                                              int32_t round_budget, unsigned long long* stats, int tile,
-                                             unsigned long long* arg = nullptr) {
+                                             unsigned long long* arg = nullptr, const int32_t* list = nullptr,
+                                             int listed = 0) {
     constexpr int kLanes = SEG < 64 ? kPackedLanes : SEG;
     constexpr int kPer = kLanes / SEG;
     const int N = f.N;
     const int tiles = (N + kPer - 1) / kPer;
     const int seg = threadIdx.x / SEG, l = threadIdx.x % SEG;
-    const int n = tile * kPer + seg;
+    const int at = tile * kPer + seg;
+    const int n = list ? list[at < listed ? at : 0] : at;
 
     extern __shared__ int32_t smem[];
     const MfLayout L = carve(smem + seg * mf_words(f.max_p, f.max_d, f.max_pd), f.max_p, f.max_d, f.max_pd);
-    bool valid = tile < tiles && n < N;
+    bool valid = list ? at < listed : tile < tiles && n < N;
     // value-only workgroup plans: bound_kernel has already written the candidates it could
     // (one candidate per workgroup, so the exit is uniform)
     if (SEG > 64 && kv_flow == nullptr && cut == nullptr && valid) {
@@ -768,8 +761,52 @@ __global__ void __launch_bounds__(SEG) maxflow_list_kernel(FlowNet f, int32_t* f
                                                            const int32_t* list, const int32_t* count) {
     const int c = *count;
     for (int idx = blockIdx.x; idx < c; idx += gridDim.x) {
-        maxflow_tile<SEG, false>(f, flow_value, nullptr, nullptr, round_budget, nullptr, list[idx]);
+        maxflow_tile<SEG, false>(f, flow_value, nullptr, nullptr, round_budget, nullptr, idx, nullptr, list, c);
         __syncthreads();  // the next candidate reuses the LDS
+    }
+}
+
+// The last kernel of hx_score_batch on replica networks: solves the candidates that net_kernel
+// listed (usually none), folding their values into the argmax slots, and reduces the slots.  With
+// nothing listed the first workgroup reduces them at once; otherwise the last workgroup to finish
+// (a ticket) does.
+template <int SEG>
+__global__ void __launch_bounds__(kPackedLanes, 8)
+    finish_kernel(FlowNet f, int32_t* flow_value, int32_t round_budget, const int32_t* list, const int32_t* count,
+                  unsigned long long* slots, int32_t* ticket, int32_t* best) {
+    static_assert(SEG <= 64, "packed plans");
+    constexpr int kPer = kPackedLanes / SEG;
+    const int c = *count;
+    if (c > 0) {
+        __shared__ int32_t last;
+        for (int t = blockIdx.x; t * kPer < c; t += gridDim.x) {
+            maxflow_tile<SEG, false, true>(f, flow_value, nullptr, nullptr, round_budget, nullptr, t, slots, list, c);
+            __syncthreads();  // the next candidates reuse the LDS
+        }
+        if (threadIdx.x == 0) {
+            __threadfence();
+            last = atomicAdd(ticket, 1) == (int32_t)gridDim.x - 1;
+            __threadfence();
+        }
+        __syncthreads();
+        if (!last) return;  // uniform
+    } else if (blockIdx.x != 0) {
+        return;
+    }
+    unsigned long long key = 0;
+#pragma unroll
+    for (int i = 0; i < kArgSlots / kPackedLanes; ++i) {
+        const unsigned long long v = __hip_atomic_load(&slots[i * kPackedLanes + threadIdx.x], __ATOMIC_RELAXED,
+                                                       __HIP_MEMORY_SCOPE_AGENT);
+        key = v > key ? v : key;
+    }
+    for (int off = 32; off > 0; off >>= 1) {
+        const unsigned long long o = __shfl_xor(key, off, 64);
+        key = o > key ? o : key;
+    }
+    if (threadIdx.x == 0) {
+        best[0] = (int32_t)(0xFFFFFFFFu - (uint32_t)key);
+        best[1] = (int32_t)((uint32_t)(key >> 32) ^ 0x80000000u);
     }
 }
 
@@ -843,6 +880,33 @@ hipError_t launch_maxflow_listed(const FlowNet& f, int32_t* flow_value, int32_t 
     else
         hipLaunchKernelGGL(maxflow_list_kernel<256>, dim3(blocks), dim3(256), lds, s, f, flow_value, round_budget, list,
                            count);
+    prof_mark(kKMaxflow, true, s);
+    return hipGetLastError();
+}
+
+hipError_t launch_finish(const Problem& p, const FlowNet& f, int32_t* flow_value, int32_t round_budget,
+                         unsigned long long* slots, const int32_t* list_count, const int32_t* list, int32_t* ticket,
+                         int32_t* best, hipStream_t s) {
+    // the networks have at most Kmax nodes in all, whatever room the caller's arrays have
+    FlowNet t = f;
+    t.max_p = t.max_d = p.Kmax;
+    t.max_pd = (p.Kmax / 2) * ((p.Kmax + 1) / 2);
+    if (t.max_pd < 1) t.max_pd = 1;
+    const int seg = segment_lanes(t.max_p, t.max_d, t.max_pd);  // at most 32 (Kmax <= 32)
+    const int per = kPackedLanes / seg;
+    const size_t lds = per * mf_words(t.max_p, t.max_d, t.max_pd) * sizeof(int32_t);
+    const int tiles = (f.N + per - 1) / per;
+    const dim3 grid(tiles < 1024 ? tiles : 1024);
+    prof_mark(kKMaxflow, false, s);
+    if (seg == 8)
+        hipLaunchKernelGGL(finish_kernel<8>, grid, dim3(kPackedLanes), lds, s, t, flow_value, round_budget, list,
+                           list_count, slots, ticket, best);
+    else if (seg == 16)
+        hipLaunchKernelGGL(finish_kernel<16>, grid, dim3(kPackedLanes), lds, s, t, flow_value, round_budget, list,
+                           list_count, slots, ticket, best);
+    else
+        hipLaunchKernelGGL(finish_kernel<32>, grid, dim3(kPackedLanes), lds, s, t, flow_value, round_budget, list,
+                           list_count, slots, ticket, best);
     prof_mark(kKMaxflow, true, s);
     return hipGetLastError();
 }

@@ -229,6 +229,58 @@ def test_score_batch_listed_kv_maximum_cluster(torch, variant):
     assert one["best"] == want["best"]
 
 
+def _feasible_problem(gpus, groups, n, slow, seed):
+    """Placements of an OPT-30B cluster of 48-80 GB GPUs, most of whose groups have a strategy, so
+    that both sides have several nodes; links slow times slower (KV edges below the node capacities)."""
+    rng = np.random.default_rng([2502, gpus, groups, n, seed])
+    nodes = (gpus + 3) // 4
+    inter = np.triu(rng.uniform(5.0, 25.0, (nodes, nodes)), 1) * 1e9
+    tab = np.array([I.GPU_TYPES[c] for c in "DEF"])
+    cl = I.cluster_from_nodes(np.repeat(np.arange(nodes) % 3, 4)[:gpus].astype(np.int32), tab, inter + inter.T)
+    cl = dataclasses.replace(cl, beta=np.ascontiguousarray(cl.beta / slow))
+    assign = rng.integers(0, groups, (gpus, n)).astype(np.uint8)
+    assign[rng.random((gpus, n)) < 0.05] = I.UNUSED
+    role = rng.integers(0, 2, (groups, n)).astype(np.uint8)
+    role[rng.random((groups, n)) < 0.05] = I.UNUSED
+    return I.Problem(cl, dict(I.OPT_30B), 700.0, 150.0, I._mask((1, 2, 3, 4, 8)), I._mask(range(1, 9)), 0, groups, assign,
+                     role)
+
+
+@pytest.mark.parametrize("gpus,groups,n,slow,room", [
+    (8, 2, 5, 1, 0), (9, 3, 17, 200, 0), (33, 7, 1000, 200, 0), (65, 16, 16384, 300, 0), (40, 17, 16385, 300, 3),
+    (64, 31, 777, 2000, 40), (129, 32, 500, 2000, 0), (24, 32, 32769, 1, 0), (64, 33, 300, 2000, 0)])
+def test_score_batch_replica_networks(torch, gpus, groups, n, slow, room):
+    """The fused network kernel around its branches: batch sizes on both sides of the switches of its
+    candidates per workgroup, group slots from two to one past its limit, 1 to 4 mask words, arrays
+    with more room than the slots need (room), and slow links, whose networks no closed form settles.
+    Rows, values and best equal the four calls' and, on a sample, the oracle's."""
+    prob = _feasible_problem(gpus, groups, n, slow, 1)
+    say(f"hx_score_batch networks: {gpus} GPUs, {groups} slots, N={n}, links / {slow}, room {room}")
+    dp = hx.DeviceProblem.upload(prob)
+    mp, md, mpd = hx.flownet_dims(groups, gpus, 0)
+    out = []
+    for fused in (False, True):
+        ws = hx.Workspace.for_problem(dp, flows=False)
+        ws.net = hx.FlowNetBuffers.empty((mp + room, md + room, max(mpd, 1) + room), n, fill=-7)
+        ws.cost.workspace.fill_(0xA5)
+        (hx.score_batch if fused else hx.score)(dp, ws)
+        torch.cuda.synchronize()
+        out.append(dict(cost={k: getattr(ws.cost, k).cpu().numpy() for k in ("tp", "pp", "bmax", "cap", "lat", "members")},
+                        net=ws.net.host(), flow_value=ws.flow_value.cpu().numpy(),
+                        best=tuple(int(x) for x in ws.best.cpu().numpy())))
+    _same(out[0], out[1], 0)
+    rows = np.arange(max(mpd, 1) + room)[:, None]
+    past = rows >= (out[1]["net"]["n_p"].astype(np.int64) * out[1]["net"]["n_d"])[None, :]
+    assert (out[1]["net"]["kv_cap"][past] == -7).all(), "a KV row past n_p n_d was written"
+    st = hx.maxflow_stats(ws.net, torch.empty_like(ws.flow_value))
+    say(f"paths: {st}")
+    if slow > 1 and groups > 3:  # a side of one node is a star
+        assert st["min_cut"] + st["push_relabel"] > n // 20, st
+    idx = np.random.default_rng(5).choice(n, min(n, 128), replace=False)
+    want = hxo.score_batch(prob.subset(idx), n_threads=N_THREADS)
+    assert np.array_equal(out[1]["flow_value"][idx], want["flow_value"])
+
+
 def test_score_batch_concurrent_streams(torch):
     """Independent calls in flight on three streams (each with its own workspace and outputs, the
     inputs shared): every stream's flow values and best equal a single-stream call's, call after
