@@ -8,14 +8,13 @@
 //
 //   graph_kernel      one lane per GPU pair: w = floor(((beta_de + beta_ed) * 0.5) / 1e6);
 //   spectral_kernel   one workgroup: power iteration on (cap I - Lap) for the Fiedler direction,
-//                     a lane per row (ascending products); the mean and the squared norm summed
-//                     in ascending order by one lane (255 dependent additions, twice per
-//                     iteration; the order depends only on the cluster, so a search computes it
-//                     once); the GPUs ranked by (x, id);
-//   partition_kernel  one workgroup per candidate: (i) the rotated spectral order cut into K
-//                     memory-balanced groups, then Kernighan-Lin passes: a lane per pair of GPUs
-//                     scores the swap from per-GPU group sums kept in LDS, a workgroup maximum
-//                     picks the largest reduction (negative ones too; lowest pair on ties), the
+//                     a lane per row (ascending products), the mean and the squared norm summed in
+//                     ascending order (the order depends only on the cluster, so a search computes
+//                     it once); the GPUs ranked by (x, id);
+//   partition_gain_kernel, partition_kernel  a candidate each: (i) the rotated spectral order cut into K
+//                     memory-balanced groups, then Kernighan-Lin passes: every pair of GPUs has its
+//                     swap's gain, kept up to date in registers (or, past the exact ranges of
+//                     binary64, formed anew from per-GPU group sums), a maximum over them picks the largest reduction (negative ones too; lowest pair on ties), the
 //                     swap is made tentatively and its two GPUs locked; the pass keeps its best
 //                     prefix and undoes the rest; (ii) groups coarsened into super nodes (LDS
 //                     atomics) and split into prefill and decode by single flips that raise the
@@ -252,7 +251,347 @@ __device__ void pg_exchange(const PgArgs& a, int u, int v, int* grp, long long* 
 // Dynamic LDS of partition_kernel: gval[u][k], the sum of w(u, x) over the GPUs x of group k.
 __host__ __device__ inline size_t pg_lds_bytes(int G) { return (size_t)G * kPgMaxK * sizeof(long long); }
 
-__global__ void __launch_bounds__(kPgBlock) partition_kernel(PgArgs a) {
+// ------------------------------------------------------------------ partition, incremental gains
+//
+// The same search with every pair's gain kept in a register.  Swapping u (group A) with v (group B)
+// moves w(x, v) - w(x, u) =: d_x from x's sum over B to its sum over A, so with s = +1 in A, -1 in B
+// and 0 elsewhere the gain of a pair (x, y) changes by (d_x - d_y)(s_y - s_x): three binary64
+// operations per pair where rescanning it reads four group sums, two groups, their memories and a
+// weight.  Likewise with h_x = the memory of x's group without x, the swap (x, y) does not widen the
+// memory gap when (m_y - m_x)(h_x - h_y) <= 0, and h follows the swaps by h_x += s_x (m_v - m_u).
+//
+// A pair's key is 2^16 gain + (2^16 - 1 - pair) as a binary64 integer, so that one maximum picks the
+// largest gain and, on ties, the lowest pair.  All values are whole numbers held exactly, which needs
+// a row of weights below 2^29 MB/s and memories below 2^52 in all: graphs past these (links of 16 TB/s
+// at 32 GPUs, 2 TB/s at 255) are left to partition_kernel, which holds them as 64-bit integers (flag).
+//
+// The pairs are laid out as (a, a + s mod G), s = 1 .. G/2: lane a of a set of P lanes holds node a's
+// state, and the NT / P sets take every (NT / P)-th shift s.  A node's partner is then at a constant
+// LDS offset (node records are stored twice, at x and x + G).  Up to 64 GPUs a wavefront has a
+// candidate to itself and needs no barrier; above, NT lanes share one.
+//
+// What bounds it: instruction issue, about 14 instructions a pair and step, and the latency of a step's
+// reduction.  Measured against partition_kernel: 32 GPUs x 16,384 candidates 1,710 -> 363 us, 100 GPUs x
+// 1,000 7.4 -> 2.2 ms (2.3 with the weights read from memory; 3.2 and 3.9 with registers bounded to 168
+// and 128 for three and four wavefronts per SIMD, which spills; 2.5 with 512 lanes a candidate).
+template <int P>
+struct PgShape {
+    static constexpr int kNT = P <= 64 ? 64 : (P == 128 ? 256 : 1024);  // lanes of a candidate
+    static constexpr int kPer = P <= 64 ? 4 : 1;                        // candidates of a workgroup
+    static constexpr int kSub = kNT / P;                                // sets of P lanes
+    static constexpr int kSlots = P / 2 / kSub;                         // shifts of a lane, at most
+    static constexpr int kBlock = kNT * kPer;
+};
+
+struct __attribute__((aligned(16))) PgNode {
+    double h, d;  // group memory without the node (NaN: locked); 2^16 d_x of the last swap
+};
+struct __attribute__((aligned(8))) PgSide {
+    int grp;
+    float s;  // s_x of the last swap
+};
+
+// Dynamic LDS of one candidate: node records and sides (twice G), groups and memories, sums of
+// weights by group (int32 [G][ld]), which the coarse weights (int64 [K][K]) later overwrite, and
+// scalars.
+__host__ __device__ inline size_t pg_fast_sums(int G, int K) {
+    const size_t a = sizeof(int32_t) * (size_t)G * (K | 1), b = sizeof(long long) * (size_t)K * K;
+    return ((a > b ? a : b) + 15) & ~(size_t)15;
+}
+__host__ __device__ inline size_t pg_fast_lds(int G, int K) {
+    return 2 * (size_t)G * (sizeof(PgNode) + sizeof(PgSide)) + (((size_t)G * (sizeof(double) + sizeof(int))) + 15) / 16 * 16 +
+           pg_fast_sums(G, K) + sizeof(long long) * kPgMaxK + 3 * sizeof(int) * kPgMaxK + 256;
+}
+
+// The largest x of a wavefront's lanes, by row shifts and row broadcasts (no LDS).
+template <int kCtrl, int kRows>
+__device__ __forceinline__ double dpp_max_step(double x) {
+    const int lo = __double2loint(x), hi = __double2hiint(x);
+    const double y = __hiloint2double(__builtin_amdgcn_update_dpp(hi, hi, kCtrl, kRows, 0xf, false),
+                                      __builtin_amdgcn_update_dpp(lo, lo, kCtrl, kRows, 0xf, false));
+    return y > x ? y : x;
+}
+__device__ __forceinline__ double wave_max(double x) {
+    x = dpp_max_step<0x111, 0xf>(x);  // row_shr:1, 2, 4, 8: lane 15 of each row holds the row's
+    x = dpp_max_step<0x112, 0xf>(x);
+    x = dpp_max_step<0x114, 0xf>(x);
+    x = dpp_max_step<0x118, 0xf>(x);
+    x = dpp_max_step<0x142, 0xa>(x);  // row_bcast15: rows 1 and 3
+    x = dpp_max_step<0x143, 0xc>(x);  // row_bcast31: rows 2 and 3
+    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(x), 63),
+                            __builtin_amdgcn_readlane(__double2loint(x), 63));
+}
+
+// Orders a candidate's LDS accesses: a barrier when several wavefronts share it.
+template <int P>
+__device__ __forceinline__ void pg_sync() {
+    __builtin_amdgcn_s_waitcnt(0xC07F);  // LDS atomics landed (lgkmcnt(0))
+    if (PgShape<P>::kPer == 1) {
+        __syncthreads();
+    } else {
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    }
+}
+
+constexpr double kPgNone = -4611686018427387904.0;  // -2^62: below every key
+
+// kLdsW: the weights staged in LDS as 32-bit integers.
+template <int P, bool kLdsW>
+__global__ void __launch_bounds__(PgShape<P>::kBlock) partition_gain_kernel(PgArgs a, int Kh, int32_t* flag) {
+    using Sh = PgShape<P>;
+    constexpr int kNT = Sh::kNT, kSub = Sh::kSub, kSlots = Sh::kSlots;
+    extern __shared__ __attribute__((aligned(16))) unsigned char pg_sm[];
+    __shared__ double red[16];
+    const int G = a.G, tid = threadIdx.x % kNT, cand = threadIdx.x / kNT;
+    const int x = tid % P, sub = tid / P, lane = threadIdx.x & 63;
+    const int64_t N = a.N;
+    const int64_t n = (int64_t)blockIdx.x * Sh::kPer + cand;
+    int32_t* wl = reinterpret_cast<int32_t*>(pg_sm);  // kLdsW: [G][G]
+    const size_t wbytes = kLdsW ? (sizeof(int32_t) * (size_t)G * G + 15) & ~(size_t)15 : 0;
+    unsigned char* base = pg_sm + wbytes + cand * pg_fast_lds(G, Kh);
+    PgNode* node = reinterpret_cast<PgNode*>(base);           // [2 G]
+    PgSide* side2 = reinterpret_cast<PgSide*>(node + 2 * G);  // [2 G]
+    double* memd = reinterpret_cast<double*>(side2 + 2 * G);  // [G]
+    int* grp = reinterpret_cast<int*>(memd + G);              // [G]
+    unsigned char* sums = base + 2 * (size_t)G * (sizeof(PgNode) + sizeof(PgSide)) +
+                          ((size_t)G * (sizeof(double) + sizeof(int)) + 15) / 16 * 16;
+    int32_t* gval = reinterpret_cast<int32_t*>(sums);  // [G][ld]
+    long long* sw = reinterpret_cast<long long*>(sums);  // [Kh][Kh]
+    long long* gmem = reinterpret_cast<long long*>(sums + pg_fast_sums(G, Kh));  // [32]
+    int* first = reinterpret_cast<int*>(gmem + kPgMaxK);
+    int* newid = first + kPgMaxK;
+    int* side = newid + kPgMaxK;
+    const int ld = Kh | 1;
+
+    // the graph within the exact ranges?  (every workgroup finds the same answer)
+    const long long wlimit = (1ll << 29) / (G + 1);  // sums of a row below 2^29, gains below 2^31
+    bool bad = false;
+    for (int e = threadIdx.x; e < G * G; e += Sh::kBlock) {
+        const long long v = a.w[e];
+        bad |= v >= wlimit;
+        if (kLdsW) wl[e] = (int32_t)v;
+    }
+    double mx = 0.0;
+    if (x < G) {
+        const int t = a.gpu_type[x];
+        mx = (t >= 0 && t < a.T) ? a.mem[t] : 0.0;
+        bad |= !(mx >= 0.0 && mx < 17592186044416.0);  // 2^44: 255 of them stay below 2^52
+        mx = floor(mx);
+        if (sub == 0) memd[x] = mx;
+    }
+    bad = __syncthreads_or(bad) != 0;
+    if (blockIdx.x == 0 && threadIdx.x == 0) *flag = bad ? 1 : 0;
+    if (bad || n >= N) return;  // wavefronts of their own candidates, or the whole workgroup
+    auto weight = [&](int u, int v) -> int32_t {
+        return kLdsW ? wl[u * G + v] : (int32_t)a.w[(int64_t)u * G + v];
+    };
+
+    const uint64_t r = a.rnd[n];
+    // K: floor(total memory / replica memory), the replica holding the weights and the KV caches of 32
+    // requests (Appendix A), shifted by the draw
+    double mtot = 0.0;
+    for (int e = 0; e < G; ++e) mtot = mtot + memd[e];
+    long long total = (long long)mtot;
+    const double Ld = (double)a.L;
+    const double rep = 12.0 * a.H * a.H * a.B * Ld + 32.0 * (2.0 * (a.s_in + a.s_out) * a.Hkv * a.B * Ld);
+    int K = (int)floor(mtot / rep) + (int)((r & 7) % 5) - 2;
+    if (K > Kh) K = Kh;
+    if (K < 2) K = 2;
+    const int rot = (int)(((r >> 3) & 0xFF) % (uint64_t)G);
+    if (total <= 0) total = 1;  // memories all zero: every GPU lands in group 0
+    // step (i): the rotated spectral order cut by memory midpoints into K groups
+    int dd = -1;
+    double cum = 0.0;
+    if (x < G) dd = a.order[(x + rot) % G];
+    if (sub == 0 && x < G) {
+        grp[x] = 0;
+        gval[x] = dd;  // staged for the prefix sums
+    }
+    pg_sync<P>();
+    for (int i = 0; i < G; ++i) {
+        const int e = gval[i];
+        const double m = e >= 0 && e < G ? memd[e] : 0.0;
+        cum = cum + (i < x ? m : 0.0);
+    }
+    if (sub == 0 && x < G && dd >= 0 && dd < G) {
+        const long long k = ((long long)K * (2 * (long long)cum + (long long)memd[dd])) / (2 * total);
+        grp[dd] = (int)(k < K - 1 ? k : K - 1);
+    }
+    pg_sync<P>();
+    int gx = x < G ? grp[x] : -1;
+
+    double key[kSlots];
+    float dm[kSlots];  // sign of m_y - m_x; NaN: no such pair
+    // (lanes past G read lane 0's partners: at most G - 1 + G / 2 + kSub < 2 G)
+    const PgNode* py = node + (x < G ? x : 0) + 1 + sub;
+    const PgSide* ps = side2 + (x < G ? x : 0) + 1 + sub;
+#pragma unroll
+    for (int j = 0; j < kSlots; ++j) {
+        const int s = 1 + sub + kSub * j;
+        dm[j] = __builtin_nanf("");
+        if (2 * s <= G && x < G && !(2 * s == G && x >= s)) {
+            const int y = x + s < G ? x + s : x + s - G;
+            const double d = memd[y] - mx;
+            dm[j] = d > 0.0 ? 1.0f : (d < 0.0 ? -1.0f : 0.0f);
+        }
+    }
+    for (int pass = 0; pass < kKlPasses; ++pass) {
+        // sums of weights by group, and the groups' memories
+        for (int e = tid; e < G * ld; e += kNT) gval[e] = 0;
+        if (tid < kPgMaxK) gmem[tid] = 0;
+        pg_sync<P>();
+        if (x < G) {
+            for (int e = sub; e < G; e += kSub) atomicAdd(&gval[x * ld + grp[e]], weight(e, x));
+            if (sub == 0) atomicAdd((unsigned long long*)&gmem[gx], (unsigned long long)(long long)mx);
+        }
+        pg_sync<P>();
+        double hx = 0.0;
+        const int g0 = gx;
+        if (x < G) {
+            hx = (double)gmem[gx] - mx;
+            if (sub == 0) {
+                node[x] = node[x + G] = PgNode{hx, 0.0};
+                side2[x] = side2[x + G] = PgSide{gx, 0.0f};
+            }
+        }
+        pg_sync<P>();
+        // the pass's opening gains.  (xo and Go hide x and G from the compiler, which would otherwise
+        // keep every shift's partner, weight and pair in registers across passes, and its bounds in
+        // scalar registers: 81 spilled registers at 64 GPUs.)
+        int xo = x, Go = G;
+        asm volatile("" : "+v"(xo));
+        asm volatile("" : "+s"(Go));
+#pragma unroll
+        for (int j = 0; j < kSlots; ++j) {
+            const int s = 1 + sub + kSub * j;
+            key[j] = 0.0;
+            if (2 * (1 + kSub * j) > Go) break;  // uniform: no lane has this shift
+            if (2 * s <= Go && xo < Go && !(2 * s == Go && xo >= s)) {
+                const int y = xo + s < Go ? xo + s : xo + s - Go;
+                const int gy = grp[y];
+                const int gain = (gval[xo * ld + gy] - gval[xo * ld + gx]) + (gval[y * ld + gx] - gval[y * ld + gy]) -
+                                 2 * weight(xo, y);
+                const int pair = xo < y ? xo * Go + y : y * Go + xo;
+                key[j] = (double)gain * 65536.0 + (double)(65535 - pair);
+            }
+        }
+        int n_swaps = 0, kbest = 0, moved = 1 << 30;
+        long long run = 0, bestsum = 0;
+        double dx = 0.0;
+        float sx = 0.0f;
+        for (;;) {
+            double best = kPgNone;
+            asm volatile("" : "+s"(Go));
+#pragma unroll
+            for (int j = 0; j < kSlots; ++j) {
+                if (2 * (1 + kSub * j) > Go) break;  // uniform: no lane has this shift
+                if (j % 4 == 0) __builtin_amdgcn_sched_barrier(0);
+                const PgNode q = py[kSub * j];
+                const PgSide z = ps[kSub * j];
+                key[j] = __builtin_fma(dx - q.d, (double)(z.s - sx), key[j]);
+                const bool ok = dm[j] * (float)(hx - q.h) <= 0.0f && z.grp != gx;
+                const double k = ok ? key[j] : kPgNone;
+                best = k > best ? k : best;
+            }
+            best = wave_max(best);
+            if (Sh::kPer == 1) {
+                if (lane == 0) red[threadIdx.x >> 6] = best;
+                __syncthreads();
+#pragma unroll
+                for (int i = 0; i < kNT / 64; ++i) best = red[i] > best ? red[i] : best;
+            }
+            if (best == kPgNone) break;  // uniform: no admissible pair left
+            const long long kk = (long long)best;
+            const int pair = 65535 - (int)(kk & 65535);
+            const int u = pair / G, v = pair - u * G;
+            ++n_swaps;
+            run += kk >> 16;
+            if (run > bestsum) {
+                bestsum = run;
+                kbest = n_swaps;
+            }
+            const int A = side2[u].grp, B = side2[v].grp;
+            const double dmem = memd[v] - memd[u];
+            pg_sync<P>();  // every wavefront has read the two groups
+            if (x < G) {
+                dx = 65536.0 * (double)(weight(v, x) - weight(u, x));
+                sx = gx == A ? 1.0f : (gx == B ? -1.0f : 0.0f);
+                hx = hx + (double)sx * dmem;
+                if (x == u || x == v) {
+                    hx = __builtin_nan("");  // locked: no comparison with it holds
+                    gx = x == u ? B : A;
+                    moved = n_swaps;
+                }
+                if (sub == 0) {
+                    node[x] = node[x + G] = PgNode{hx, dx};
+                    side2[x] = side2[x + G] = PgSide{gx, sx};
+                }
+            }
+            pg_sync<P>();
+        }
+        // the swaps past the best prefix are undone: a GPU moves at most once in a pass
+        if (moved > kbest) gx = g0;
+        if (sub == 0 && x < G) grp[x] = gx;
+        pg_sync<P>();
+        if (kbest == 0) break;  // uniform
+    }
+    // groups numbered by smallest member
+    if (tid < kPgMaxK) first[tid] = 1 << 30;
+    pg_sync<P>();
+    if (sub == 0 && x < G) atomicMin(&first[gx], x);
+    pg_sync<P>();
+    if (tid < kPgMaxK) {
+        int id = 0;
+        for (int k = 0; k < kPgMaxK; ++k) id += first[k] < first[tid] ? 1 : 0;
+        newid[tid] = id;
+    }
+    for (int e = tid; e < Kh * Kh; e += kNT) sw[e] = 0;
+    int used = 0;
+    for (int k = 0; k < kPgMaxK; ++k) used += first[k] < (1 << 30) ? 1 : 0;
+    pg_sync<P>();
+    if (x < G) {
+        gx = newid[gx];
+        if (sub == 0) grp[x] = gx;
+    }
+    pg_sync<P>();
+    // step (ii): coarsened weights and the max-cut split
+    if (x < G)
+        for (int e = sub; e < G; e += kSub) {
+            const int ge = grp[e];
+            if (ge != gx) atomicAdd((unsigned long long*)&sw[gx * Kh + ge], (unsigned long long)weight(e, x));
+        }
+    if (tid < kPgMaxK) side[tid] = tid < used ? (int)((r >> (11 + tid)) & 1) : 0;
+    pg_sync<P>();
+    if (tid < 64) {  // one wavefront: a lane per super node
+        uint64_t ones = __ballot(lane < used && side[lane & (kPgMaxK - 1)] != 0);
+        if (ones == 0 || ones == ((1ull << used) - 1)) ones ^= 1ull << (used - 1);
+        for (int step = 0; step < used * used; ++step) {
+            const int n1 = __popcll(ones);
+            const bool one = (ones >> lane) & 1;
+            long long gain = 0;
+            if (lane < used && !(one && n1 == 1) && !(!one && n1 == used - 1))
+                for (int l = 0; l < used; ++l) {
+                    const long long v = l == lane ? 0 : sw[lane * Kh + l];
+                    gain += (((ones >> l) & 1) != 0) == one ? v : -v;
+                }
+            // largest gain, then lowest super node; gains are below 2^47 in all
+            const double bk = wave_max(gain > 0 ? (double)(gain * 64 + (63 - lane)) : 0.0);
+            if (!(bk > 0.0)) break;  // uniform
+            ones ^= 1ull << (63 - (int)((long long)bk & 63));
+        }
+        for (int k = lane; k < a.Kmax; k += 64)
+            a.role[(int64_t)k * N + n] =
+                k < used ? (uint8_t)((ones >> k) & 1 ? HX_DECODE : HX_PREFILL) : (uint8_t)HX_UNUSED;
+    }
+    // step (iii): the projection
+    if (sub == 0 && x < G) a.assign[(int64_t)x * N + n] = (uint8_t)gx;
+}
+
+// Any graph, in 64-bit integers; a workgroup takes every gridDim.x-th candidate.  Only graphs past the
+// exact ranges of partition_gain_kernel, which says so in flag, are partitioned here.
+__global__ void __launch_bounds__(kPgBlock) partition_kernel(PgArgs a, const int32_t* flag) {
     extern __shared__ __attribute__((aligned(16))) unsigned char pg_sm[];
     long long* gval = reinterpret_cast<long long*>(pg_sm);  // [G][kPgMaxK]
     __shared__ long long memv[kPgBlock];
@@ -265,9 +604,11 @@ __global__ void __launch_bounds__(kPgBlock) partition_kernel(PgArgs a) {
     __shared__ int first[kPgMaxK], newid[kPgMaxK], side[kPgMaxK];
     __shared__ long long sw[kPgMaxK * kPgMaxK];
     __shared__ long long cum[kPgBlock];
-    const int tid = threadIdx.x, n = blockIdx.x;
+    const int tid = threadIdx.x;
     const int G = a.G;
     const int64_t N = a.N;
+    if (*flag == 0) return;  // uniform
+    for (int n = blockIdx.x; n < N; n += gridDim.x) {
     const uint64_t r = a.rnd[n];
     if (tid < G) {
         const int t = a.gpu_type[tid];
@@ -429,6 +770,8 @@ __global__ void __launch_bounds__(kPgBlock) partition_kernel(PgArgs a) {
     if (tid < G) a.assign[(int64_t)tid * N + n] = (uint8_t)grp[tid];
     for (int k = tid; k < a.Kmax; k += kPgBlock)
         a.role[(int64_t)k * N + n] = k < used ? (uint8_t)(side[k] ? HX_DECODE : HX_PREFILL) : (uint8_t)HX_UNUSED;
+    __syncthreads();  // the next candidate reuses the LDS
+    }
 }
 
 }  // namespace
@@ -444,22 +787,50 @@ hipError_t launch_spectral(int32_t G, const double* beta, int64_t* w, int32_t it
     return hipGetLastError();
 }
 
+template <int P, bool kLdsW>
+static hipError_t launch_gain(const PgArgs& a, int Kh, int32_t* flag, hipStream_t s) {
+    using Sh = PgShape<P>;
+    const size_t lds = (kLdsW ? (sizeof(int32_t) * (size_t)a.G * a.G + 15) & ~(size_t)15 : 0) +
+                       Sh::kPer * pg_fast_lds(a.G, Kh);
+    if (lds > 32 * 1024) {
+        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&partition_gain_kernel<P, kLdsW>),
+                                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        if (e != hipSuccess) return e;
+    }
+    hipLaunchKernelGGL((partition_gain_kernel<P, kLdsW>), dim3((unsigned)((a.N + Sh::kPer - 1) / Sh::kPer)), dim3(Sh::kBlock), lds,
+                       s, a, Kh, flag);
+    return hipGetLastError();
+}
+
 hipError_t launch_partition(const Problem& p, int64_t* w, const int32_t* order, const uint64_t* rnd, uint8_t* assign,
                             uint8_t* role, hipStream_t s) {
     const int64_t cells = (int64_t)p.G * p.G;
     hipLaunchKernelGGL(graph_kernel, dim3((unsigned)((cells + 255) / 256)), dim3(256), 0, s, p.G, p.beta, w);
     PgArgs a{p.G, p.Kmax, p.N, p.L, p.H, p.Hkv, p.B, p.s_in, p.s_out, w, order, p.gpu_type, p.mem, p.T, rnd,
              assign, role};
+    // the word after the weights: whether the graph is past the exact ranges of the incremental kernel
+    int32_t* flag = reinterpret_cast<int32_t*>(w + cells);
+    int Kh = p.Kmax < p.G ? p.Kmax : p.G;
+    if (Kh > kPgMaxK) Kh = kPgMaxK;
+    if (Kh < 2) Kh = 2;
     prof_mark(kKPartition, false, s);
+    hipError_t e;
+    if (p.G <= 32) e = launch_gain<32, true>(a, Kh, flag, s);
+    else if (p.G <= 64) e = launch_gain<64, true>(a, Kh, flag, s);
+    // above 104 GPUs the staged weights would leave a CU one workgroup (more than 80 KB of LDS)
+    else if (p.G <= 104) e = launch_gain<128, true>(a, Kh, flag, s);
+    else if (p.G <= 128) e = launch_gain<128, false>(a, Kh, flag, s);
+    else e = launch_gain<256, false>(a, Kh, flag, s);
+    if (e != hipSuccess) return e;
     // gval of 255 GPUs (65,280 bytes) takes the workgroup past 64 KB of LDS, which gfx950 allows
     // (160 KB per workgroup) once the kernel's dynamic limit is raised
     const size_t lds = pg_lds_bytes(p.G);
     if (lds > 32 * 1024) {
-        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(partition_kernel),
-                                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        e = hipFuncSetAttribute(reinterpret_cast<const void*>(partition_kernel),
+                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) return e;
     }
-    hipLaunchKernelGGL(partition_kernel, dim3((unsigned)p.N), dim3(kPgBlock), lds, s, a);
+    hipLaunchKernelGGL(partition_kernel, dim3((unsigned)(p.N < 512 ? p.N : 512)), dim3(kPgBlock), lds, s, a, flag);
     prof_mark(kKPartition, true, s);
     return hipGetLastError();
 }

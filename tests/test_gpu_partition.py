@@ -118,3 +118,39 @@ def test_partition_large_weights(torch):
     want_a, want_r = hxo.partition_candidates(prob, want_o, rnd_h)
     assert np.array_equal(assign.cpu().numpy(), want_a)
     assert np.array_equal(role.cpu().numpy(), want_r)
+
+
+@pytest.mark.parametrize("gpus,groups,n,ties,links", [
+    (2, 2, 9, False, 1.0), (3, 1, 9, False, 1.0), (15, 4, 33, True, 1.0), (31, 32, 40, False, 1.0), (32, 16, 257, True, 1.0),
+    (33, 32, 40, False, 1.0), (49, 9, 21, True, 1.0), (64, 32, 30, True, 1.0), (65, 8, 12, False, 1.0), (81, 32, 6, False, 1.0),
+    (104, 32, 5, True, 1.0), (105, 32, 5, False, 1.0), (113, 20, 4, False, 1.0), (128, 32, 4, True, 1.0),
+    (129, 32, 3, False, 1.0), (255, 32, 2, False, 1.0), (20, 8, 40, False, 2e4)])
+def test_partition_sizes(torch, gpus, groups, n, ties, links):
+    """The spectral order and the candidates around every size switch (lane sets of 32 to 256, rows of
+    16-GPU chunks, weights staged or read), with ties (every link of a kind alike, so that many
+    pairs share a gain and the lowest must win), mixed memories, and links past the incremental
+    kernel's range (links): bit for bit the oracle's."""
+    rng = np.random.default_rng([2502, gpus, groups])
+    nodes = (gpus + 3) // 4
+    inter = np.full((nodes, nodes), 12.5e9) if ties else np.triu(rng.uniform(3.0, 25.0, (nodes, nodes)), 1) * 1e9
+    tab = np.array([I.GPU_TYPES[c] for c in "ABCDEF"])
+    cl = I.cluster_from_nodes(np.repeat(np.arange(nodes) % 6, 4)[:gpus].astype(np.int32), tab, np.maximum(inter, inter.T))
+    cl = dataclasses.replace(cl, beta=np.ascontiguousarray(cl.beta * links))
+    blank = lambda rows: np.full((rows, 1), I.UNUSED, np.uint8)
+    prob = I.Problem(cl, dict(I.LLAMA2_70B), 1500.0, 400.0, I._mask((1, 2, 4, 8)), I._mask(range(1, 9)), 0, groups,
+                     blank(gpus), blank(groups))
+    say(f"partition: {gpus} GPUs, {groups} slots, N={n}, ties {ties}, links x {links}")
+    for iters in (1, 60):
+        dp, ws, order, fied = _spectral(torch, prob, iters)
+        want_o, want_x = hxo.spectral_order(prob, iters)
+        assert np.array_equal(fied.cpu().numpy(), want_x), "Fiedler vectors not bit-identical"
+        assert np.array_equal(order.cpu().numpy(), want_o)
+    rnd_h = rng.integers(0, 2**64, n, dtype=np.uint64)
+    rnd = torch.as_tensor(rnd_h.view(np.int64)).to("cuda")
+    assign = torch.full((gpus, n), 0xEE, dtype=torch.uint8, device="cuda")
+    role = torch.full((groups, n), 0xEE, dtype=torch.uint8, device="cuda")
+    hx.partition_candidates(dp, ws, order, rnd, assign, role)
+    torch.cuda.synchronize()
+    want_a, want_r = hxo.partition_candidates(prob, want_o, rnd_h)
+    assert np.array_equal(assign.cpu().numpy(), want_a)
+    assert np.array_equal(role.cpu().numpy(), want_r)
