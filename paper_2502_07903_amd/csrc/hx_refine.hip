@@ -9,9 +9,9 @@
 //                  spare capacity, or its tail reaches its head in the residual graph.
 //
 //   classes_kernel  one workgroup per candidate: the residual graph of the flow given by
-//                   kv_flow (node flows follow by conservation), its transitive closure as
-//                   bitset rows in LDS (one Warshall pass, a lane per row), then the class of
-//                   every edge;
+//                   kv_flow (node flows follow by conservation), contracted to the replicas' KV
+//                   sides, its transitive closure as bitset rows in LDS (64 pivots at a time), then
+//                   the class of every edge;
 //   moves_kernel    one workgroup per (parent, 256 children): the parent's donor GPUs,
 //                   receiver groups and flip-eligible groups, listed in ascending id in LDS;
 //                   then a lane per child applies one MOVE, SWAP or FLIP chosen by its draw;
@@ -21,9 +21,6 @@
 
 namespace hx {
 namespace {
-
-constexpr int kClsBlock = 256;
-constexpr int kClsWords = kClsMaxV / 64;  // bitset words per closure row
 
 __device__ __forceinline__ void drain_barrier() {
     // LDS atomics with unused results must have landed before the workgroup reads their
@@ -40,116 +37,201 @@ struct ClsArgs {
     uint8_t* kv_cls;
 };
 
-__global__ void __launch_bounds__(kClsBlock) classes_kernel(ClsArgs a) {
-    __shared__ uint64_t reach[kClsMaxV * kClsWords];  // row u: the vertices u reaches
-    __shared__ int32_t pf[HX_MAX_GPUS + 1], df[HX_MAX_GPUS + 1];
+// The closure runs on the contracted residual graph: a replica's coordinator-side vertex (prefill in,
+// decode out) has one neighbour on either side, so reachability through it follows from the node
+// flows, and the vertices kept are din(j) = j, pout(i) = D + i, s = P + D and t = s + 1 (at most 257)
+// with
+//   pout(i) -> din(j) when the KV edge has room, din(j) -> pout(i) when it carries flow;
+//   s -> pout(i) when source and node edge have room, pout(i) -> s when prefill i carries flow;
+//   din(j) -> t when node and sink edge have room, t -> din(j) when decode j carries flow.
+// A wavefront per network takes at most 64 nodes (kBlock 64), a workgroup of four 255.
+template <int kBlock>
+struct ClsShape {
+    static constexpr int kNodes = kBlock == 64 ? 64 : kClsMaxV / 2 - 1;
+    static constexpr int kRows = kNodes + 2;
+    static constexpr int kWords = (kRows + 63) / 64;  // bitset words per row
+    static constexpr int kStride = kWords | 1;        // odd, so that the rows of a wavefront's lanes spread over the banks
+};
+
+__device__ __forceinline__ uint64_t lane_word(uint64_t v, int k) {
+    return ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(v >> 32), k) << 32) |
+           (uint32_t)__builtin_amdgcn_readlane((int)v, k);
+}
+
+// acc | OR over the set bits k < nk of m of v's value in lane k (m: this lane's mask; nk a multiple
+// of 8 at most 64).
+__device__ __forceinline__ uint64_t or_lanes(uint64_t acc, uint64_t m, uint64_t v, int nk) {
+    for (int k0 = 0; k0 < nk; k0 += 8)
+#pragma unroll
+        for (int x = 0; x < 8; ++x) acc |= (0 - ((m >> (k0 + x)) & 1)) & lane_word(v, k0 + x);
+    return acc;
+}
+
+// Transitive closure of V rows of kW words (row stride kS), 64 pivots at a time: the pivots'
+// own 64 x 64 block is closed in registers (a lane per row, Warshall's order, no barrier: every
+// wavefront forms it itself), the pivot rows take the rows that this block reaches, then every other
+// row takes the pivot rows its word of the block names.  Three barriers per 64 vertices where one
+// pivot at a time takes 64.
+template <int kW, int kS, int kBlock>
+__device__ void closure(uint64_t* reach, int V) {
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    for (int kb = 0; kb < kW; ++kb) {
+        const int nk = V - 64 * kb < 64 ? V - 64 * kb : 64, nk8 = (nk + 7) & ~7;
+        uint64_t* prow = reach + (64 * kb + lane) * kS;
+        uint64_t d = lane < nk ? prow[kb] : 0;
+        if (kW > 1) __syncthreads();  // every wavefront has the block
+        for (int k0 = 0; k0 < nk8; k0 += 8)
+#pragma unroll
+            for (int x = 0; x < 8; ++x) d |= (0 - ((d >> (k0 + x)) & 1)) & lane_word(d, k0 + x);
+        for (int w = wave; w < kW; w += kBlock / 64) {
+            if (w == kb) {
+                if (lane < nk) prow[w] = d;
+                continue;
+            }
+            const uint64_t v = lane < nk ? prow[w] : 0;
+            const uint64_t acc = or_lanes(v, d, v, nk8);
+            if (lane < nk) prow[w] = acc;
+        }
+        __syncthreads();
+        if (kW == 1) return;
+        for (int u = tid; u < V; u += kBlock) {
+            if ((u >> 6) == kb) continue;
+            uint64_t* ru = reach + u * kS;
+            const uint64_t m = ru[kb];
+            uint64_t acc[kW];
+#pragma unroll
+            for (int w = 0; w < kW; ++w) acc[w] = ru[w];
+            for (int k = 0; k < nk; ++k) {
+                const uint64_t on = 0 - ((m >> k) & 1);
+                const uint64_t* rk = reach + (64 * kb + k) * kS;
+#pragma unroll
+                for (int w = 0; w < kW; ++w) acc[w] |= rk[w] & on;
+            }
+#pragma unroll
+            for (int w = 0; w < kW; ++w) ru[w] = acc[w];
+        }
+        __syncthreads();
+    }
+}
+
+// What bounds it: the closure's instructions, and the loads of the KV rows (one 4-byte word of a
+// cache line each; the XCD-aware order lets neighbouring candidates share the lines in one L2).  Each
+// KV row is read once: a wavefront per prefill node turns it into bit words with ballots.  Measured
+// against a closure of all 2 + 2 (P + D) vertices by one pivot per barrier that read the KV rows seven
+// times: one network of 128 GPUs 181 -> 34 us, 8,192 networks of 64 GPUs' replicas 200 -> 28 us, 4,096 of
+// 16 to 64 nodes a side 855 -> 130 us.
+template <int kBlock>
+__global__ void __launch_bounds__(kBlock) classes_kernel(ClsArgs a) {
+    using Sh = ClsShape<kBlock>;
+    constexpr int kS = Sh::kStride;
+    __shared__ uint64_t reach[Sh::kRows * kS];                      // row u: the vertices u reaches
+    __shared__ uint64_t some[Sh::kNodes][(Sh::kNodes + 63) / 64];  // prefill i: its KV edges of capacity >= 1
+    __shared__ int32_t pf[Sh::kNodes], df[Sh::kNodes];
     const FlowNet& f = a.f;
-    const int n = blockIdx.x, tid = threadIdx.x;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int64_t N = f.N;
+    const int chunk = (int)((N + 7) / 8);
+    const int n = (int)(blockIdx.x & 7) * chunk + (int)(blockIdx.x >> 3);
+    if ((int)(blockIdx.x >> 3) >= chunk || n >= N) return;  // uniform
     const int P = f.n_p[n], D = f.n_d[n];
     // a network that does not fit its arrays or the closure's LDS rows, or whose max-flow
     // failed, gets no classes
-    if (P < 0 || D < 0 || P > f.max_p || D > f.max_d || P * D > f.max_pd || 2 + 2 * (P + D) > kClsMaxV ||
+    if (P < 0 || D < 0 || P > f.max_p || D > f.max_d || P * D > f.max_pd || P + D > Sh::kNodes ||
         a.flow_value[n] < 0) {
-        for (int r = tid; r < f.max_p + f.max_d; r += kClsBlock) a.node_cls[(int64_t)r * N + n] = 0;
+        for (int r = tid; r < f.max_p + f.max_d; r += kBlock) a.node_cls[(int64_t)r * N + n] = 0;
         return;
     }
-    const int V = 2 + 2 * (P + D);
-    const int W = (V + 63) >> 6;
-    auto pin = [](int i) { return 2 + 2 * i; };
-    auto pout = [](int i) { return 3 + 2 * i; };
-    auto din = [P](int j) { return 2 + 2 * P + 2 * j; };
-    auto dout = [P](int j) { return 3 + 2 * P + 2 * j; };
-    auto kvf = [&](int i, int j) { return a.kv_flow[(int64_t)(i * D + j) * N + n]; };
-    auto kvc = [&](int i, int j) { return f.kv_cap[(int64_t)(i * D + j) * N + n]; };
-
-    // node flows by conservation: prefill i carries its KV row's sum, decode j its column's
-    for (int i = tid; i < P; i += kClsBlock) {
-        int32_t s = 0;
-        for (int j = 0; j < D; ++j) s += kvf(i, j);
-        pf[i] = s;
-    }
-    for (int j = tid; j < D; j += kClsBlock) {
-        int32_t s = 0;
-        for (int i = 0; i < P; ++i) s += kvf(i, j);
-        df[j] = s;
-    }
+    const int V = P + D + 2, W = (V + 63) >> 6, vs = P + D, vt = vs + 1;
+    for (int e = tid; e < V * kS; e += kBlock) reach[e] = 0;
+    for (int j = tid; j < D; j += kBlock) df[j] = 0;
     __syncthreads();
-
-    // residual arcs: u -> v when flow < capacity, v -> u when flow > 0; each lane owns its rows
-    for (int u = tid; u < V; u += kClsBlock) {
-        uint64_t* row = reach + u * kClsWords;
-        for (int w = 0; w < W; ++w) row[w] = 0;
-        auto set = [row](int v) { row[v >> 6] |= 1ull << (v & 63); };
-        set(u);
-        if (u == 0) {
-            for (int i = 0; i < P; ++i)
-                if (pf[i] < f.src_cap[(int64_t)i * N + n]) set(pin(i));
-        } else if (u == 1) {
-            for (int j = 0; j < D; ++j)
-                if (df[j] > 0) set(dout(j));
-        } else if (u < 2 + 2 * P) {
-            const int i = (u - 2) >> 1;
-            if ((u & 1) == 0) {  // prefill in-node
-                if (pf[i] < f.p_cap[(int64_t)i * N + n]) set(pout(i));
-                if (pf[i] > 0) set(0);
-            } else {             // prefill out-node
-                for (int j = 0; j < D; ++j)
-                    if (kvf(i, j) < kvc(i, j)) set(din(j));
-                if (pf[i] > 0) set(pin(i));
+    // a wavefront per prefill node: its KV row's bit words, its flow (the row's sum), and the decode
+    // nodes' flows and reverse arcs
+    for (int i = wave; i < P; i += kBlock / 64) {
+        uint64_t* row = reach + (D + i) * kS;
+        int32_t sum = 0;
+        for (int j0 = 0; j0 < D; j0 += 64) {
+            const int j = j0 + lane;
+            const int64_t o = (int64_t)(i * D + (j < D ? j : D - 1)) * N + n;
+            const int32_t fl = j < D ? a.kv_flow[o] : 0, c = j < D ? f.kv_cap[o] : 0;
+            const uint64_t room = __ballot(fl < c), any = __ballot(c >= 1);
+            if (lane == 0) {
+                row[j0 >> 6] |= room;
+                some[i][j0 >> 6] = any;
             }
-        } else {
-            const int j = (u - 2 - 2 * P) >> 1;
-            if ((u & 1) == 0) {  // decode in-node
-                if (df[j] < f.d_cap[(int64_t)j * N + n]) set(dout(j));
-                for (int i = 0; i < P; ++i)
-                    if (kvf(i, j) > 0) set(pout(i));
-            } else {             // decode out-node
-                if (df[j] < f.sink_cap[(int64_t)j * N + n]) set(1);
-                if (df[j] > 0) set(din(j));
-            }
+            sum += fl;
+            if (fl != 0) atomicAdd(&df[j], fl);
+            if (fl > 0)
+                atomicOr((unsigned long long*)&reach[j * kS + ((D + i) >> 6)], 1ull << ((D + i) & 63));
         }
+        for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off, 64);
+        if (lane == 0) pf[i] = sum;
     }
-    // transitive closure (Warshall): after step k every row holds the vertices it reaches
-    // through intermediates < k + 1.  Row k does not change in step k, so lanes update their
-    // own rows from it concurrently.
-    for (int k = 0; k < V; ++k) {
-        __syncthreads();
-        const uint64_t* rk = reach + k * kClsWords;
-        for (int u = tid; u < V; u += kClsBlock) {
-            if (u == k) continue;
-            uint64_t* ru = reach + u * kClsWords;
-            if ((ru[k >> 6] >> (k & 63)) & 1ull)
-                for (int w = 0; w < W; ++w) ru[w] |= rk[w];
-        }
-    }
-    __syncthreads();
-
-    auto reaches = [](int u, int v) { return (int)((reach[u * kClsWords + (v >> 6)] >> (v & 63)) & 1ull); };
-    auto cls = [&](int u, int v, int32_t fl, int32_t c) {
-        int k = reaches(0, u) & reaches(v, 1);
-        if (c >= 1 && (fl < c || reaches(u, v))) k |= 2;
-        return k;
+    drain_barrier();
+    // the arcs at s and t, and every vertex reaching itself
+    auto set = [&](int u, int v) {
+        atomicOr((unsigned long long*)&reach[u * kS + (v >> 6)], 1ull << (v & 63));
     };
-    for (int i = tid; i < P; i += kClsBlock) {
+    for (int u = tid; u < V; u += kBlock) set(u, u);
+    for (int i = tid; i < P; i += kBlock) {
         const int64_t o = (int64_t)i * N + n;
-        int k = cls(pin(i), pout(i), pf[i], f.p_cap[o]) | (cls(0, pin(i), pf[i], f.src_cap[o]) << 2);
-        int kvb = 0;
-        if (reaches(0, pout(i)))
-            for (int j = 0; j < D && !kvb; ++j) kvb = reaches(din(j), 1);
-        a.node_cls[o] = (uint8_t)(k | (kvb << 4));
+        if (pf[i] < f.src_cap[o] && pf[i] < f.p_cap[o]) set(vs, D + i);
+        if (pf[i] > 0) set(D + i, vs);
     }
-    for (int j = tid; j < D; j += kClsBlock) {
+    for (int j = tid; j < D; j += kBlock) {
         const int64_t o = (int64_t)j * N + n;
-        int k = cls(din(j), dout(j), df[j], f.d_cap[o]) | (cls(dout(j), 1, df[j], f.sink_cap[o]) << 2);
-        int kvb = 0;
-        if (reaches(din(j), 1))
-            for (int i = 0; i < P && !kvb; ++i) kvb = reaches(0, pout(i));
-        a.node_cls[(int64_t)(f.max_p + j) * N + n] = (uint8_t)(k | (kvb << 4));
+        if (df[j] < f.d_cap[o] && df[j] < f.sink_cap[o]) set(j, vt);
+        if (df[j] > 0) set(vt, j);
     }
-    for (int e = tid; e < P * D; e += kClsBlock) {
-        const int i = e / D, j = e - i * D;
-        a.kv_cls[(int64_t)e * N + n] = (uint8_t)cls(pout(i), din(j), kvf(i, j), kvc(i, j));
+    drain_barrier();
+    if (W == 1) closure<1, kS, kBlock>(reach, V);
+    else if (W == 2) closure<2, kS, kBlock>(reach, V);
+    else if constexpr (Sh::kWords > 2) {
+        if (W == 3) closure<3, kS, kBlock>(reach, V);
+        else closure<Sh::kWords, kS, kBlock>(reach, V);
+    }
+
+    auto reaches = [](int u, int v) { return (int)((reach[u * kS + (v >> 6)] >> (v & 63)) & 1ull); };
+    // bit 0: bottleneck (s reaches the tail, the head reaches t); bit 1: underutilized (capacity c >= 1
+    // and room left, or the tail reaches the head otherwise: `around`, asked of saturated edges)
+    auto cls = [](int tail, int head, int32_t fl, int32_t c, int around) {
+        return (tail & head) | (c >= 1 && (fl < c || around) ? 2 : 0);
+    };
+    const int st = reaches(vs, vt);
+    bool any_p = false, any_d = false;  // some pout that s reaches, some din that reaches t
+    for (int w = 0; w < W; ++w) {
+        const int lo = 64 * w;
+        const uint64_t dins = D - lo >= 64 ? ~0ull : (D > lo ? (1ull << (D - lo)) - 1 : 0);
+        const uint64_t core = vs - lo >= 64 ? ~0ull : (vs > lo ? (1ull << (vs - lo)) - 1 : 0);
+        any_p |= (reach[vs * kS + w] & core & ~dins) != 0;
+    }
+    for (int j0 = 0; j0 < D; j0 += 64) any_d |= __any(j0 + lane < D && reaches(j0 + lane < D ? j0 + lane : 0, vt)) != 0;
+    for (int i = tid; i < P; i += kBlock) {
+        const int64_t o = (int64_t)i * N + n;
+        const int32_t fl = pf[i], cp = f.p_cap[o], cs = f.src_cap[o];
+        const int s_out = reaches(vs, D + i), out_t = reaches(D + i, vt);
+        const int s_in = (fl < cs) | (s_out & (fl > 0));                    // s reaches the in-node
+        const int in_t = ((fl < cp) & out_t) | ((fl > 0) & st);             // the in-node reaches t
+        const int k = cls(s_in, out_t, fl, cp, s_out) | (cls(1, in_t, fl, cs, s_out) << 2);
+        a.node_cls[o] = (uint8_t)(k | ((s_out && any_d ? 1 : 0) << 4));
+    }
+    for (int j = tid; j < D; j += kBlock) {
+        const int64_t o = (int64_t)j * N + n;
+        const int32_t fl = df[j], cd = f.d_cap[o], ct = f.sink_cap[o];
+        const int s_in = reaches(vs, j), in_t = reaches(j, vt);
+        const int out_t = (fl < ct) | (in_t & (fl > 0));                    // the out-node reaches t
+        const int s_out = ((fl < cd) & s_in) | ((fl > 0) & st);             // s reaches the out-node
+        const int k = cls(s_in, out_t, fl, cd, in_t) | (cls(s_out, 1, fl, ct, in_t) << 2);
+        a.node_cls[(int64_t)(f.max_p + j) * N + n] = (uint8_t)(k | ((in_t && any_p ? 1 : 0) << 4));
+    }
+    // a KV edge with room is an arc of the closure, so its second bit is capacity and reachability
+    for (int i = wave; i < P; i += kBlock / 64) {
+        const int s_out = reaches(vs, D + i);
+        for (int j = lane; j < D; j += 64) {
+            const int c1 = (int)((some[i][j >> 6] >> (j & 63)) & 1);
+            a.kv_cls[(int64_t)(i * D + j) * N + n] =
+                (uint8_t)((s_out & reaches(j, vt)) | ((c1 & reaches(D + i, j)) << 1));
+        }
     }
 }
 
@@ -327,8 +409,14 @@ __global__ void gather_kernel(int G, int K, int Ns, const uint8_t* sa, const uin
 hipError_t launch_classes(const FlowNet& f, const int32_t* flow_value, const int32_t* kv_flow, uint8_t* node_cls,
                           uint8_t* kv_cls, hipStream_t s) {
     prof_mark(kKClasses, false, s);
-    hipLaunchKernelGGL(classes_kernel, dim3(f.N), dim3(kClsBlock), 0, s,
-                       ClsArgs{f, flow_value, kv_flow, node_cls, kv_cls});
+    const ClsArgs a{f, flow_value, kv_flow, node_cls, kv_cls};
+    const dim3 grid(8 * (unsigned)(((int64_t)f.N + 7) / 8));  // XCD-aware order
+    // one wavefront per network where the arrays hold at most 64 nodes in all: at most two bit words a
+    // row, and several networks per CU
+    if (f.max_p + f.max_d <= 64)
+        hipLaunchKernelGGL(classes_kernel<64>, grid, dim3(64), 0, s, a);
+    else
+        hipLaunchKernelGGL(classes_kernel<256>, grid, dim3(256), 0, s, a);
     prof_mark(kKClasses, true, s);
     return hipGetLastError();
 }

@@ -92,6 +92,35 @@ def test_edge_classes_random_networks(torch):
     compare_classes(fn, node.cpu().numpy(), kv.cpu().numpy(), hxo.edge_classes(fn))
 
 
+@pytest.mark.parametrize("P,D,room", [(1, 1, 0), (31, 31, 0), (30, 33, 0), (32, 32, 0), (31, 33, 1), (31, 32, 3), (62, 64, 0),
+                                      (64, 64, 0), (120, 62, 0), (95, 66, 0), (200, 30, 0), (25, 230, 0), (230, 25, 0)])
+def test_edge_classes_closure_blocks(torch, P, D, room):
+    """Networks of P x D nodes around the closure's sizes: one to five words a row, the last vertices on
+    either side of a 64-pivot block, one wavefront or four per network (by the room of the arrays),
+    with capacities small enough that edges saturate everywhere; every class equal to the oracle's."""
+    rng = np.random.default_rng([91, P, D])
+    N, mp, md = (21 if P + D < 132 else 4), P + room, D
+    mpd = mp * md
+    fn = dict(n_p=np.full(N, P, np.int32), n_d=np.full(N, D, np.int32), dims=(mp, md, mpd))
+    for k, rows in (("src_cap", mp), ("p_cap", mp), ("d_cap", md), ("sink_cap", md), ("kv_cap", mpd),
+                    ("p_slot", mp), ("d_slot", md)):
+        hi = rng.choice([1, 3, 50, 10 ** 5], size=N)
+        fn[k] = (rng.random((rows, N)) * (hi[None, :] + 1)).astype(np.int32)
+        if k in ("src_cap", "sink_cap"):
+            fn[k] = np.where(rng.random((rows, N)) < 0.5, Hh.CAP_MAX, fn[k]).astype(np.int32)
+    fn["n_p"][::5] = np.maximum(P - np.arange(len(fn["n_p"][::5])), 0)
+    nb = hx.FlowNetBuffers.from_host(fn)
+    fv = torch.empty(N, dtype=torch.int32, device="cuda")
+    kvf = torch.zeros((mpd, N), dtype=torch.int32, device="cuda")
+    say(f"edge classes: {P} x {D} nodes, room {room}")
+    hx.maxflow_batch(nb, fv, kvf)
+    node = torch.full((mp + md, N), 0xEE, dtype=torch.uint8, device="cuda")
+    kv = torch.full((mpd, N), 0xEE, dtype=torch.uint8, device="cuda")
+    hx.edge_classes(nb, fv, kvf, node, kv)
+    torch.cuda.synchronize()
+    compare_classes(fn, node.cpu().numpy(), kv.cpu().numpy(), hxo.edge_classes(fn))
+
+
 def test_edge_classes_beyond_closure_rows(torch):
     """A network of more than 255 nodes gets no classes (node rows 0); its neighbours do."""
     mp, md = 200, 100
