@@ -12,7 +12,8 @@
 // from the source, decode node d sends b_d = min(d_cap, sink) to the sink, and c_pd are the
 // KV edges.  The contracted graph is bipartite: s -> P -> D -> t.
 //
-// Algorithm (Goldberg-Tarjan push-relabel, in synchronous rounds).  The source sits at
+// Algorithm (Goldberg-Tarjan push-relabel, in synchronous rounds; the packed plans' form -- the workgroup
+// plans run on bit words, push_relabel_bits).  The source sits at
 // height V = P + D + 2, the sink at 0.  A round has two phases separated by barriers:
 //   P-phase: each active prefill node pushes along its admissible arcs (to decode nodes one
 //            level lower, then back to the source), then relabels if excess remains;
@@ -68,21 +69,27 @@ __host__ __device__ inline size_t mf_words(int max_p, int max_d, int max_pd) {
     return 2 * ((size_t)max_pd + max_p) + 4 * (size_t)max_p + 4 * (size_t)max_d + 4;
 }
 
-__device__ inline MfLayout carve(int32_t* sm, int max_p, int max_d, int max_pd) {
+__device__ inline MfLayout carve(int32_t* sm, int max_p, int max_d, int max_pd, bool heights) {
     MfLayout L;
     const int arc = max_pd + max_p;  // P*(D|1) <= P*D + P
     L.cap = sm;
     L.fl = L.cap + arc;
     L.a = L.fl + arc;
-    L.fs = L.a + max_p;
+    L.fs = heights ? L.a + max_p : L.a;
     L.ep = L.fs + max_p;
     L.hp = L.ep + max_p;
-    L.b = L.hp + max_p;
+    L.b = heights ? L.hp + max_p : L.hp;
     L.ft = L.b + max_d;
     L.ed = L.ft + max_d;
     L.hd = L.ed + max_d;
-    L.misc = L.hd + max_d;
+    L.misc = heights ? L.hd + max_d : L.hd;
     return L;
+}
+// Plans whose every network runs on bit words (workgroup plans of at most 256 rows a side) need no
+// heights, and the source flows can take the place of the source capacities (they start equal, and
+// whoever changes the flows has read the capacities): four networks of 128 GPUs then share a CU, not three.
+__host__ __device__ inline bool mf_heights(int seg, int max_p, int max_d) {
+    return seg <= 64 || max_p > seg || max_d > seg;
 }
 
 // Exact heights by label-correcting sweeps: hd = 1 where d -> t has residual, hp = V + 1 where
@@ -117,6 +124,327 @@ __device__ void global_relabel(const MfLayout& L, int l, int P, int D, int Ds, i
             }
         }
         if (!__syncthreads_or(changed)) break;
+    }
+}
+
+// Push-relabel of the workgroup plans, by one wavefront of the workgroup: lane l owns prefill and
+// decode nodes l, l + 64, ... (up to SEG a side), with the residual arcs as bit words: room[i] the
+// decode nodes that prefill i can still push to, used[j] the prefill nodes that decode j holds flow of.
+// Exact distances to the sink are formed anew in every round, a level at a time: a node joins the
+// level when its words meet the last level's (a ballot per 64 nodes), and the bits that met are its
+// admissible arcs.  A phase then walks those arcs alone, four at a time so that their LDS reads
+// overlap.  Excess that cannot reach the sink stays where it is and is taken back at the end: a decode
+// node returns it over its used arcs and a prefill node to the source, which leaves a maximum flow of
+// the same value (when only the value is asked for, it is left).
+// What bounds it: the latency of the dependent LDS accesses along a node's arcs; one wavefront needs
+// no barrier, and the networks in flight are bound by their LDS (four per CU at 128 GPUs).  4,096
+// networks of 16 to 64 nodes a side 1,836 -> 366 us, against a lane per node that scanned its whole row in
+// every push and every sweep of a global relabel, with barriers between the phases (two wavefronts and
+// barriers on bit words: 492).
+template <int SEG>
+struct MfBits {
+    static constexpr int kM = SEG / 64;
+    uint64_t room[SEG][kM], used[SEG][kM];
+};
+
+__device__ __forceinline__ void mf_wave_sync() {
+    __builtin_amdgcn_s_waitcnt(0xC07F);  // LDS atomics landed (lgkmcnt(0))
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// The bit words of the flow in L, by every lane l of the workgroup (followed by a barrier).
+template <int SEG>
+__device__ __forceinline__ void residual_bits(MfBits<SEG>& S, const MfLayout& L, int l, int P, int D, int Ds) {
+    constexpr int kM = MfBits<SEG>::kM;
+    if (l < P)
+#pragma unroll
+        for (int w = 0; w < kM; ++w) {
+            uint64_t m = 0;
+            const int hi = D - 64 * w < 64 ? D - 64 * w : 64;
+            for (int x = 0; x < hi; ++x) m |= (uint64_t)(L.cap[l * Ds + 64 * w + x] - L.fl[l * Ds + 64 * w + x] > 0) << x;
+            S.room[l][w] = m;
+        }
+    if (l < D)
+#pragma unroll
+        for (int w = 0; w < kM; ++w) {
+            uint64_t m = 0;
+            const int hi = P - 64 * w < 64 ? P - 64 * w : 64;
+            for (int x = 0; x < hi; ++x) m |= (uint64_t)(L.fl[(64 * w + x) * Ds + l] > 0) << x;
+            S.used[l][w] = m;
+        }
+}
+
+// Decode node j returns up to e of its excess over the arcs of word w in m; returns the rest.
+template <int SEG, bool kStats>
+__device__ __forceinline__ int32_t push_back(MfBits<SEG>& S, const MfLayout& L, int j, int w, uint64_t m, int32_t e,
+                                             int Ds, unsigned long long& pushes) {
+    while (m && e > 0) {
+        int x[4], n = 0;
+        int32_t f0[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            x[k] = m ? __builtin_ctzll(m) : (k ? x[k - 1] : 0);
+            n += m != 0;
+            m &= m - 1;  // 0 stays 0
+            f0[k] = L.fl[(64 * w + x[k]) * Ds + j];
+        }
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const int32_t amt = k < n ? (f0[k] < e ? f0[k] : e) : 0;
+            if (amt > 0) {
+                const int i = 64 * w + x[k];
+                L.fl[i * Ds + j] = f0[k] - amt;
+                e -= amt;
+                atomicAdd(&L.ep[i], amt);
+                atomicOr((unsigned long long*)&S.room[i][j >> 6], 1ull << (j & 63));
+                if (amt == f0[k]) atomicAnd((unsigned long long*)&S.used[j][w], ~(1ull << x[k]));
+                if (kStats) ++pushes;
+            }
+        }
+    }
+    return e;
+}
+
+// Returns whether active excess is left (the round budget ran out).  One wavefront; S holds the bit
+// words of L's flow.
+template <int SEG, bool kStats>
+__device__ bool push_relabel_bits(MfBits<SEG>& S, const MfLayout& L, int l, int P, int D, int Ds, int32_t round_budget,
+                                  bool settle, unsigned long long* stats) {
+    constexpr int kM = MfBits<SEG>::kM;
+    unsigned long long pushes = 0, relabels = 0;
+    int32_t b[kM], ft[kM];
+    int old_p[kM] = {}, old_d[kM] = {};  // kStats: the last distances
+#pragma unroll
+    for (int s = 0; s < kM; ++s) {
+        b[s] = l + 64 * s < D ? L.b[l + 64 * s] : 0;
+        ft[s] = 0;
+    }
+    bool left = false;
+    for (int round = 0;; ++round) {
+        // distances and admissible arcs
+        int dp[kM], dd[kM];  // 0: does not reach the sink
+        uint64_t ap[kM][kM], ad[kM][kM], front[kM];
+        int32_t ep[kM], ed[kM];
+#pragma unroll
+        for (int s = 0; s < kM; ++s) {
+            const int v = l + 64 * s;
+            ep[s] = v < P ? L.ep[v] : 0;
+            ed[s] = v < D ? L.ed[v] : 0;
+            dp[s] = 0;
+            dd[s] = v < D && b[s] - ft[s] > 0 ? 1 : 0;
+#pragma unroll
+            for (int w = 0; w < kM; ++w) ap[s][w] = ad[s][w] = 0;
+            front[s] = __ballot(dd[s] == 1);
+        }
+        for (int lv = 1;; lv += 2) {
+            uint64_t any = 0, fp[kM];
+#pragma unroll
+            for (int s = 0; s < kM; ++s) {
+                const int v = l + 64 * s;
+                bool hit = false;
+                if (v < P && dp[s] == 0) {
+#pragma unroll
+                    for (int w = 0; w < kM; ++w) {
+                        ap[s][w] = S.room[v][w] & front[w];
+                        hit |= ap[s][w] != 0;
+                    }
+                    if (hit) dp[s] = lv + 1;
+                }
+                fp[s] = __ballot(hit);
+                any |= fp[s];
+            }
+            if (!any) break;
+            any = 0;
+#pragma unroll
+            for (int s = 0; s < kM; ++s) {
+                const int v = l + 64 * s;
+                bool hit = false;
+                if (v < D && dd[s] == 0) {
+#pragma unroll
+                    for (int w = 0; w < kM; ++w) {
+                        ad[s][w] = S.used[v][w] & fp[w];
+                        hit |= ad[s][w] != 0;
+                    }
+                    if (hit) dd[s] = lv + 2;
+                }
+                front[s] = __ballot(hit);
+                any |= front[s];
+            }
+            if (!any) break;
+        }
+        bool active = false;
+#pragma unroll
+        for (int s = 0; s < kM; ++s) {
+            active |= (ep[s] > 0 && dp[s] > 0) || (ed[s] > 0 && dd[s] > 0);
+            if (kStats) {
+                relabels += (dp[s] != old_p[s] && round > 0) + (dd[s] != old_d[s] && round > 0);
+                old_p[s] = dp[s];
+                old_d[s] = dd[s];
+            }
+        }
+        if (!__any(active)) break;
+        if (round == round_budget) {
+            left = true;
+            break;
+        }
+        if (kStats && l == 0) {
+            atomicAdd(&stats[HX_MF_ROUNDS], 1ull);
+            atomicAdd(&stats[HX_MF_GLOBAL_RELABELS], 1ull);
+        }
+        // prefill nodes push one level down
+#pragma unroll
+        for (int s = 0; s < kM; ++s) {
+            if (!(ep[s] > 0 && dp[s] > 0)) continue;
+            const int v = l + 64 * s;
+            const int32_t* c = L.cap + v * Ds;
+            int32_t* fr = L.fl + v * Ds;
+            int32_t e = ep[s];
+#pragma unroll
+            for (int w = 0; w < kM; ++w) {
+                uint64_t full = 0, m = ap[s][w];
+                while (m && e > 0) {
+                    int x[4], n = 0;
+                    int32_t f0[4], r0[4];
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) {
+                        x[k] = m ? __builtin_ctzll(m) : (k ? x[k - 1] : 0);
+                        n += m != 0;
+                        m &= m - 1;
+                        f0[k] = fr[64 * w + x[k]];
+                        r0[k] = c[64 * w + x[k]];
+                    }
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) {
+                        const int32_t rest = r0[k] - f0[k], amt = k < n ? (rest < e ? rest : e) : 0;
+                        if (amt > 0) {
+                            const int j = 64 * w + x[k];
+                            fr[j] = f0[k] + amt;
+                            e -= amt;
+                            atomicAdd(&L.ed[j], amt);
+                            atomicOr((unsigned long long*)&S.used[j][v >> 6], 1ull << (v & 63));
+                            if (amt == rest) full |= 1ull << x[k];
+                            if (kStats) ++pushes;
+                        }
+                    }
+                }
+                if (full) S.room[v][w] &= ~full;
+            }
+            L.ep[v] = e;
+        }
+        mf_wave_sync();
+        // decode nodes push to the sink, or back to prefill nodes one level down
+#pragma unroll
+        for (int s = 0; s < kM; ++s) {
+            const int v = l + 64 * s;
+            int32_t e = v < D ? L.ed[v] : 0;
+            if (!(e > 0 && dd[s] > 0)) continue;
+            if (dd[s] == 1) {
+                const int32_t rest = b[s] - ft[s], amt = rest < e ? rest : e;
+                ft[s] += amt;
+                e -= amt;
+                if (kStats) ++pushes;
+            } else {
+#pragma unroll
+                for (int w = 0; w < kM; ++w)
+                    e = push_back<SEG, kStats>(S, L, v, w, ad[s][w], e, Ds, pushes);
+            }
+            L.ed[v] = e;
+        }
+        mf_wave_sync();
+    }
+    if (settle && !left) {
+        // excess that cannot reach the sink goes back: decode to prefill, then prefill to the source
+#pragma unroll
+        for (int s = 0; s < kM; ++s) {
+            const int v = l + 64 * s;
+            int32_t e = v < D ? L.ed[v] : 0;
+            if (e <= 0) continue;
+            for (int w = 0; w < kM; ++w) e = push_back<SEG, kStats>(S, L, v, w, S.used[v][w], e, Ds, pushes);
+            L.ed[v] = 0;
+        }
+        mf_wave_sync();
+#pragma unroll
+        for (int s = 0; s < kM; ++s) {
+            const int v = l + 64 * s;
+            const int32_t e = v < P ? L.ep[v] : 0;
+            if (e <= 0) continue;
+            L.fs[v] -= e;
+            L.ep[v] = 0;
+            if (kStats) ++pushes;
+        }
+    }
+#pragma unroll
+    for (int s = 0; s < kM; ++s)
+        if (l + 64 * s < D) L.ft[l + 64 * s] = ft[s];
+    if (kStats) {
+        if (pushes) atomicAdd(&stats[HX_MF_PUSHES], pushes);
+        if (relabels) atomicAdd(&stats[HX_MF_RELABELS], relabels);
+    }
+    return left;
+}
+
+// The canonical minimum cut of the flow in L, by one wavefront on the residual bit words: the same
+// reachability as maxflow_tile's sweeps, a level at a time.  A reached prefill out-node offers its word
+// of decode in-nodes with room, a reached decode in-node its word of prefill nodes it holds flow of;
+// the in- and out-node of a chain follow from its flow.
+template <int SEG>
+__device__ void cut_bits(const MfBits<SEG>& S, const MfLayout& L, const FlowNet& f, uint8_t* cut, int n, int l, int P,
+                         int D) {
+    constexpr int kM = MfBits<SEG>::kM;
+    const int64_t N = f.N;
+    bool pin[kM], pout[kM], din[kM], fresh[kM];
+    int32_t fs[kM];
+#pragma unroll
+    for (int s = 0; s < kM; ++s) {
+        const int v = l + 64 * s;
+        const int64_t o = (int64_t)v * N + n;
+        fs[s] = v < P ? L.fs[v] : 0;
+        pin[s] = v < P && f.src_cap[o] - fs[s] > 0;
+        pout[s] = fresh[s] = pin[s] && f.p_cap[o] - fs[s] > 0;
+        din[s] = false;
+    }
+    // the OR over the fresh nodes' words: word w in lane w
+    auto offered = [&](const uint64_t (*words)[kM], uint64_t (&out)[kM]) {
+#pragma unroll
+        for (int w = 0; w < kM; ++w) {
+            uint64_t m = 0;
+#pragma unroll
+            for (int s = 0; s < kM; ++s)
+                if (fresh[s]) m |= words[l + 64 * s][w];
+            for (int off = 32; off > 0; off >>= 1) m |= __shfl_xor((unsigned long long)m, off, 64);
+            out[w] = m;
+        }
+    };
+    for (;;) {
+        uint64_t m[kM];
+        offered(S.room, m);
+        bool any = false;
+#pragma unroll
+        for (int s = 0; s < kM; ++s) {
+            fresh[s] = l + 64 * s < D && !din[s] && ((m[s] >> l) & 1);
+            din[s] |= fresh[s];
+            any |= fresh[s];
+        }
+        if (!__any(any)) break;
+        offered(S.used, m);
+        any = false;
+#pragma unroll
+        for (int s = 0; s < kM; ++s) {
+            fresh[s] = l + 64 * s < P && !pout[s] && ((m[s] >> l) & 1);
+            pout[s] |= fresh[s];
+            any |= fresh[s];
+        }
+        if (!__any(any)) break;
+    }
+#pragma unroll
+    for (int s = 0; s < kM; ++s) {
+        const int v = l + 64 * s;
+        const int64_t o = (int64_t)v * N + n;
+        pin[s] |= pout[s] && fs[s] > 0;
+        if (v < P) cut[o] = (uint8_t)((pin[s] ? 1 : 0) | (pout[s] ? 2 : 0));
+        if (v < D) cut[(int64_t)f.max_p * N + o] = (uint8_t)((din[s] ? 1 : 0) | (din[s] && f.d_cap[o] - L.ft[v] > 0 ? 2 : 0));
     }
 }
 
@@ -256,7 +584,8 @@ __device__ __forceinline__ void maxflow_tile(const FlowNet& f, int32_t* flow_val
     const int n = list ? list[at < listed ? at : 0] : at;
 
     extern __shared__ int32_t smem[];
-    const MfLayout L = carve(smem + seg * mf_words(f.max_p, f.max_d, f.max_pd), f.max_p, f.max_d, f.max_pd);
+    const MfLayout L = carve(smem + seg * mf_words(f.max_p, f.max_d, f.max_pd), f.max_p, f.max_d, f.max_pd,
+                             mf_heights(SEG, f.max_p, f.max_d));
     bool valid = list ? at < listed : tile < tiles && n < N;
     // value-only workgroup plans: bound_kernel has already written the candidates it could
     // (one candidate per workgroup, so the exit is uniform)
@@ -341,6 +670,7 @@ __device__ __forceinline__ void maxflow_tile(const FlowNet& f, int32_t* flow_val
         L.fs[i] = a;  // saturate every source edge
         L.ep[i] = a;
     }
+    bool thin = false;  // some KV arc below min(a_i, b_j)
     if (SEG <= 64) {
 #pragma unroll
         for (int r = 0; r < kKvRows; ++r) {
@@ -351,12 +681,25 @@ __device__ __forceinline__ void maxflow_tile(const FlowNet& f, int32_t* flow_val
                 L.fl[i * Ds + d] = 0;
             }
         }
-    } else {
-        const bool need_kv = has_flow || kv_flow != nullptr || cut != nullptr;
-        for (int e = l; need_kv && e < P * D; e += SEG) {
-            const int i = e / D, d = e - i * D;
-            L.cap[i * Ds + d] = f.kv_cap[(int64_t)e * N + n];
-            L.fl[i * Ds + d] = 0;
+    } else if (has_flow || kv_flow != nullptr || cut != nullptr) {
+        // sixteen rows' loads in flight per lane (rows past the last read it again and are dropped); the
+        // dominance test on the way
+        constexpr int kBatch = 16;
+        const int E = P * D;
+        for (int e0 = l; e0 < E; e0 += kBatch * SEG) {
+            int32_t v[kBatch];
+#pragma unroll
+            for (int x = 0; x < kBatch; ++x) v[x] = f.kv_cap[(int64_t)(e0 + x * SEG < E ? e0 + x * SEG : E - 1) * N + n];
+#pragma unroll
+            for (int x = 0; x < kBatch; ++x) {
+                const int e = e0 + x * SEG;
+                if (e < E) {
+                    const int i = e / D, d = e - i * D;
+                    L.cap[i * Ds + d] = v[x];
+                    L.fl[i * Ds + d] = 0;
+                    thin |= v[x] < (L.a[i] < L.b[d] ? L.a[i] : L.b[d]);
+                }
+            }
         }
     }
     __syncthreads();
@@ -375,7 +718,6 @@ __device__ __forceinline__ void maxflow_tile(const FlowNet& f, int32_t* flow_val
         const uint64_t ba = (__ballot(l < P && L.a[l] > 0) >> sh) & segmask;
         const uint64_t bb = (__ballot(l < D && L.b[l] > 0) >> sh) & segmask;
         const bool one_p = __popcll(ba) == 1, one_d = __popcll(bb) == 1;
-        bool thin = false;  // some KV arc below min(a_i, b_j)
 #pragma unroll
         for (int r = 0; r < kKvRows; ++r) {
             const int e = l + r * SEG;
@@ -505,12 +847,6 @@ __device__ __forceinline__ void maxflow_tile(const FlowNet& f, int32_t* flow_val
     } else {
         // Workgroup plans (one candidate per workgroup, so every branch here is uniform).
         __shared__ long long wave_sum[SEG > 64 ? SEG / 64 : 1];
-        bool thin = false;
-        for (int e = l; has_flow && e < P * D; e += SEG) {
-            const int i = e / D, d = e - i * D;
-            const int32_t m = L.a[i] < L.b[d] ? L.a[i] : L.b[d];
-            thin |= L.cap[i * Ds + d] < m;
-        }
         if (!__syncthreads_or(thin) && has_flow) {
             path = HX_MF_DOMINANT;
             // block scan: lane l owns a contiguous run of nodes on each side; clamped inclusive
@@ -567,10 +903,23 @@ __device__ __forceinline__ void maxflow_tile(const FlowNet& f, int32_t* flow_val
 
     const int V = P + D + 2;
     const int INF = 2 * V + 2;
-    bool active = false;
+    bool active = false, left = false;  // left: out of rounds (push_relabel_bits)
     for (int i = l; i < P; i += SEG) active |= L.ep[i] > 0;
     unsigned long long pushes = 0, relabels = 0;  // kStats
     if (kStats && valid && l == 0) atomicAdd(&stats[path], 1ull);
+    __shared__ MfBits<(SEG > 64 ? SEG : 64)> B;  // (workgroup plans)
+    if constexpr (SEG > 64) {
+        // (more than SEG nodes a side, which only arrays wider than 256 rows hold, stay with the loop below)
+        if (path == HX_MF_PUSH_RELABEL && P <= SEG && D <= SEG) {  // uniform: one candidate per workgroup
+            residual_bits<SEG>(B, L, l, P, D, Ds);
+            __syncthreads();
+            if (threadIdx.x < 64)
+                left = push_relabel_bits<SEG, kStats>(B, L, l, P, D, Ds, round_budget,
+                                                      kv_flow != nullptr || cut != nullptr, stats);
+            __syncthreads();
+            active = false;
+        }
+    }
     for (int round = 0; __syncthreads_or(active) && round < round_budget; ++round) {
         if (kStats && threadIdx.x == 0) {
             atomicAdd(&stats[HX_MF_ROUNDS], 1ull);
@@ -666,7 +1015,7 @@ __device__ __forceinline__ void maxflow_tile(const FlowNet& f, int32_t* flow_val
     // Flow value = total flow into the sink; a candidate still holding excess ran out of rounds.
     for (int j = l; j < D; j += SEG)
         if (L.ft[j] > 0) atomicAdd(&L.misc[0], L.ft[j]);
-    if (active) L.misc[1] = 1;
+    if (active || left) L.misc[1] = 1;
     __syncthreads();
     const int32_t value = cut_value >= 0 ? cut_value : (L.misc[1] ? HX_ENOCONV : L.misc[0]);
     if (valid && l == 0) flow_value[n] = value;
@@ -678,6 +1027,16 @@ __device__ __forceinline__ void maxflow_tile(const FlowNet& f, int32_t* flow_val
         }
     if (!cut) return;  // uniform across the workgroup
 
+    if constexpr (SEG > 64) {
+        if (P <= SEG && D <= SEG) {
+            if (path != HX_MF_PUSH_RELABEL) {  // uniform
+                residual_bits<SEG>(B, L, l, P, D, Ds);
+                __syncthreads();
+            }
+            if (threadIdx.x < 64) cut_bits<SEG>(B, L, f, cut, n, l, P, D);
+            return;
+        }
+    }
     // Canonical minimum cut: reachability from s in the residual graph of the uncontracted
     // network, by sweeps until nothing changes.  Reuses a/ep (prefill in/out flags) and
     // b/ed (decode in/out flags); source/node/sink capacities are reloaded.
@@ -826,12 +1185,19 @@ __global__ void clear_stats_kernel(unsigned long long* stats) {
     if (threadIdx.x < HX_MF_STATS) stats[threadIdx.x] = 0;
 }
 
+// Dynamic LDS of a launch: per candidates of a workgroup.
+size_t mf_launch_lds(int seg, int per, const FlowNet& f) {
+    const size_t words = mf_words(f.max_p, f.max_d, f.max_pd);
+    const size_t spare = mf_heights(seg, f.max_p, f.max_d) ? 0 : 2 * (size_t)f.max_p + f.max_d;  // hp, hd and fs
+    return per * (words - spare) * sizeof(int32_t);
+}
+
 template <int SEG>
 hipError_t launch_seg(const FlowNet& f, int32_t* fv, int32_t* kv, uint8_t* cut, int32_t budget,
                       unsigned long long* stats, unsigned long long* arg, hipStream_t s) {
     constexpr int kLanes = SEG < 64 ? kPackedLanes : SEG;
     constexpr int kPer = kLanes / SEG;
-    const size_t lds = kPer * mf_words(f.max_p, f.max_d, f.max_pd) * sizeof(int32_t);
+    const size_t lds = mf_launch_lds(SEG, kPer, f);
     const int tiles = (f.N + kPer - 1) / kPer;
     const int blocks = 8 * ((tiles + 7) / 8);
     prof_mark(kKMaxflow, false, s);
@@ -871,7 +1237,7 @@ bool maxflow_workgroup_plan(int32_t max_p, int32_t max_d, int32_t max_pd) {
 hipError_t launch_maxflow_listed(const FlowNet& f, int32_t* flow_value, int32_t round_budget, const int32_t* list,
                                  const int32_t* count, hipStream_t s) {
     const int seg = segment_lanes(f.max_p, f.max_d, f.max_pd);
-    const size_t lds = mf_words(f.max_p, f.max_d, f.max_pd) * sizeof(int32_t);
+    const size_t lds = mf_launch_lds(seg, 1, f);
     const int blocks = f.N < 2048 ? f.N : 2048;  // eight workgroups per CU at most
     prof_mark(kKMaxflow, false, s);
     if (seg == 128)

@@ -423,6 +423,42 @@ def test_maxflow_round_budget_reports_noconv(torch, monkeypatch):
     assert np.array_equal(fv[ok], want["flow_value"][ok])
 
 
+@pytest.mark.parametrize("P,D,rows", [(40, 3, 65), (64, 64, 65), (65, 60, 65), (128, 30, 128), (30, 128, 128), (129, 28, 129),
+                                      (25, 200, 200), (255, 20, 255), (17, 9, 300)])
+def test_maxflow_workgroup_plans(torch, monkeypatch, P, D, rows):
+    """Binding networks on the workgroup plans (arrays of `rows` rows a side: 65 to 128 take 128 lanes and two
+    bit words a node, up to 256 four; 300 rows are past the bit words): values equal the oracle's with and
+    without flows, the flows are valid maximum flows and the cut is the canonical one; with a budget of
+    one round some networks report HX_ENOCONV and the others their value."""
+    rng = np.random.default_rng([77, P, D])
+    N, mpd = 40, P * D
+    n_p = np.maximum(1, P - rng.integers(0, 3, N)).astype(np.int32)
+    n_d = np.maximum(1, D - rng.integers(0, 3, N)).astype(np.int32)
+    fn = dict(n_p=n_p, n_d=n_d, dims=(rows, rows, mpd))
+    for k, r in (("src_cap", rows), ("p_cap", rows), ("d_cap", rows), ("sink_cap", rows), ("kv_cap", mpd),
+                 ("p_slot", rows), ("d_slot", rows)):
+        fn[k] = rng.integers(0, 1000, (r, N)).astype(np.int32)
+    fn["kv_cap"] = (fn["kv_cap"] * rng.choice([0.02, 0.2, 1.0], N)).astype(np.int32)
+    want = hxo.maxflow_batch(fn)
+    nb = hx.FlowNetBuffers.from_host(fn)
+    say(f"max-flow: {P} x {D} nodes in {rows} rows")
+    fv = torch.empty(N, dtype=torch.int32, device="cuda")
+    kv = torch.zeros((mpd, N), dtype=torch.int32, device="cuda")
+    cut = torch.zeros((2 * rows, N), dtype=torch.uint8, device="cuda")
+    hx.maxflow_batch(nb, fv)
+    assert np.array_equal(fv.cpu().numpy(), want["flow_value"])
+    hx.maxflow_batch(nb, fv, kv, cut)
+    torch.cuda.synchronize()
+    assert np.array_equal(fv.cpu().numpy(), want["flow_value"])
+    Hh.check_flow(fn, fv.cpu().numpy(), kv.cpu().numpy(), cut.cpu().numpy(), idx=range(0, N, 3))
+    monkeypatch.setenv("HX_MAXFLOW_ROUND_BUDGET", "1")
+    hx.maxflow_batch(nb, fv, kv, cut)
+    got = fv.cpu().numpy()
+    assert (got == hx.HX_ENOCONV).any()
+    ok = got != hx.HX_ENOCONV
+    assert np.array_equal(got[ok], want["flow_value"][ok])
+
+
 def test_deterministic(torch):
     prob = I.make_problem(3, n_cand=4096)
     say("determinism")
