@@ -676,6 +676,11 @@ __device__ __forceinline__ uint32_t set_nib(uint32_t v, int i, int x) {
     return (v & ~(15u << (4 * i))) | ((uint32_t)x << (4 * i));
 }
 
+// (edge, candidate) lanes of a workgroup, whose searches run one after another: few, because a handful
+// of hard edges in one workgroup sets the kernel's time.  With 64, 16, 8, 4 lanes: 2.41, 1.67, 1.36,
+// 1.32 ms at 32 GPUs x 16,384 candidates; whole calls with 64 and 8: 3.64 and 2.44 ms at x 65,536, 5.59
+// and 1.95 ms at 64 GPUs x 4,096.
+constexpr int kOrderLanes = 8;
 constexpr int kOrderThreads = 256;  // kv_order_kernel: wave 0 holds the lanes, all four waves search
 constexpr int kOrderLevels = 4;     // search levels below a queued prefix, at most
 constexpr int kOrderQueue = 2 * kOrderThreads;  // prefixes handed out per edge, at least (when nx allows)
@@ -685,11 +690,11 @@ struct OrderShared {
     double blk[kBlockPairs * kOrderStages * kOrderStages];  // [pair][X stage][Y stage]
     double lbsave[kOrderLevels * kOrderThreads];             // [level][thread]: row bound before the level
     uint64_t mksave[kOrderLevels * kOrderThreads];           // [level][thread]: final-row mask before it
-    double t[kKvBlock];                                      // lanes' ascending-order times
+    double t[kOrderLanes];                                      // lanes' ascending-order times
     double best, glb;
     uint32_t colord[kBlockPairs * kOrderStages];  // [pair][Y stage]: X stages by ascending block time
-    int32_t shape[kKvBlock];                      // lanes' ptp | ppp << 8 | dtp << 16 | dpp << 24
-    int32_t list[kKvBlock];                       // lanes whose edge is searched
+    int32_t shape[kOrderLanes];                      // lanes' ptp | ppp << 8 | dtp << 16 | dpp << 24
+    int32_t list[kOrderLanes];                       // lanes whose edge is searched
     int32_t px[kBlockPairs], py[kBlockPairs], pn[kBlockPairs];
     int32_t ystart[kOrderStages + 1];  // first pair of each Y position
     int32_t yfin[kOrderStages + 1];    // rows below yfin[d] are final once X positions 0..d-1 are assigned
@@ -805,8 +810,8 @@ __device__ __forceinline__ void order_search(OrderShared& S, int nx, int ny, int
     }
 }
 
-// One lane per (KV edge, candidate), as kv_kernel, with the stage-order search: the lanes (wave 0
-// of a 256-thread workgroup) first take their ascending-order times; then all four waves search
+// One lane per (KV edge, candidate), as kv_kernel, with the stage-order search: the kOrderLanes lanes (of
+// a 256-thread workgroup) first take their ascending-order times; then all four waves search
 // the edge of each lane whose replicas are not both single-stage, one edge at a time.  The block
 // table of that edge goes to LDS, and the orders of the side with fewer stages (X) are searched
 // position by position: row y of C is final once every X position sharing layers with y is
@@ -820,10 +825,10 @@ __global__ void __launch_bounds__(kOrderThreads) kv_order_kernel(Problem p, Cost
     OrderShared& S = *reinterpret_cast<OrderShared*>(sm);
     uint8_t* mem = sm + kOrderLds;
     const int tid = threadIdx.x;
-    const int stride = kKvBlock;
-    const int64_t gid = (int64_t)blockIdx.x * kKvBlock + tid;
+    const int stride = kOrderLanes;
+    const int64_t gid = (int64_t)blockIdx.x * kOrderLanes + tid;
     const int64_t N = p.N;
-    bool live = tid < kKvBlock && gid < (int64_t)f.max_pd * N;
+    bool live = tid < kOrderLanes && gid < (int64_t)f.max_pd * N;
     const int e = live ? (int)(gid / N) : 0;
     const int n = live ? (int)(gid - (int64_t)e * N) : 0;
     const int np = live ? f.n_p[n] : 0, nd = live ? f.n_d[n] : 0;
@@ -847,7 +852,7 @@ __global__ void __launch_bounds__(kOrderThreads) kv_order_kernel(Problem p, Cost
     }
     if (tid == 0) S.count = 0;
     __syncthreads();
-    if (tid < kKvBlock) {
+    if (tid < kOrderLanes) {
         S.t[tid] = t;
         S.shape[tid] = ptp | ppp << 8 | dtp << 16 | dpp << 24;
         if (feas && (ppp > 1 || dpp > 1)) S.list[atomicAdd(&S.count, 1)] = tid;
@@ -1582,7 +1587,7 @@ hipError_t launch_w(const Problem& p, const CostOut& o, const FlowNet& f, hipStr
     launch_nodes<W>(p, o, f, s);
     prof_mark(kKNodes, true, s);
     const int64_t lanes = (int64_t)f.max_pd * p.N;
-    const int blocks = (int)((lanes + kKvBlock - 1) / kKvBlock);
+    const int blocks = (int)((lanes + kOrderLanes - 1) / kOrderLanes);
     // kv_kernel: a grid row per KV row a replica network can have (its n_p + n_d <= Kmax nodes
     // give at most floor(Kmax/2) ceil(Kmax/2) <= 16,256 rows, within the grid's y limit)
     const int64_t rows_pd = (int64_t)(p.Kmax / 2) * ((p.Kmax + 1) / 2);
@@ -1599,7 +1604,8 @@ hipError_t launch_w(const Problem& p, const CostOut& o, const FlowNet& f, hipStr
             e = table ? launch_kv_gpu<W, false, true>(p, f, o, s) : launch_kv_gpu<W, false, false>(p, f, o, s);
         if (e != hipSuccess) return e;
     } else if (p.variant & HX_VARIANT_KV_ORDER) {
-        hipLaunchKernelGGL(kv_order_kernel<W>, dim3(blocks), dim3(kOrderThreads), kOrderLds + lds, s, p, o, f);
+        hipLaunchKernelGGL(kv_order_kernel<W>, dim3(blocks), dim3(kOrderThreads),
+                           kOrderLds + 2 * (size_t)p.G * kOrderLanes, s, p, o, f);
     } else if (p.variant & HX_VARIANT_ASYM) {
         hipLaunchKernelGGL((kv_kernel<W, true, false>), grid_kv, dim3(kKvBlock), lds + sizeof(double) * p.G, s, p,
                            o, f);

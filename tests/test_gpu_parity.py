@@ -424,7 +424,7 @@ def test_maxflow_round_budget_reports_noconv(torch, monkeypatch):
 
 
 @pytest.mark.parametrize("P,D,rows", [(40, 3, 65), (64, 64, 65), (65, 60, 65), (128, 30, 128), (30, 128, 128), (129, 28, 129),
-                                      (25, 200, 200), (255, 20, 255), (17, 9, 300)])
+                                      (25, 200, 200), (255, 20, 255), (220, 32, 220), (17, 9, 300)])
 def test_maxflow_workgroup_plans(torch, monkeypatch, P, D, rows):
     """Binding networks on the workgroup plans (arrays of `rows` rows a side: 65 to 128 take 128 lanes and two
     bit words a node, up to 256 four; 300 rows are past the bit words): values equal the oracle's with and
