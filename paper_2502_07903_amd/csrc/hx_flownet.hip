@@ -1077,8 +1077,9 @@ __device__ __forceinline__ void lane_sync() {
 // values, where nodes_kernel, kv_kernel and the max-flow kernel would each read the network back.
 //   nodes   256 / C lanes per candidate take the group slots; a slot's node index is the number of
 //           its side's slots below it, from bit masks met in LDS;
-//   rows    every KV row below n_p n_d is written 0, those lanes taking the rows in turn, then the edges whose two replicas have a strategy are walked and
-//           written over them (a barrier orders the two stores);
+//   rows    every KV row below n_p n_d is written 0, those lanes taking the rows in turn, then the
+//           edges whose two replicas have a strategy are walked and written over them (a barrier
+//           orders the two stores);
 //   walks   kWalkLanes lanes per edge over the workgroup's edges (a candidate has |feasible prefill|
 //           x |feasible decode| of them, found by a search in the prefix sums of these counts).
 //           The rank pairs (head slices of ptp x dtp) are the same for every stage pair, so lane l
@@ -1097,8 +1098,9 @@ __device__ __forceinline__ void lane_sync() {
 // are stars, so the value costs a few LDS operations where the max-flow kernel loaded every row of
 // the plan.  Measured against the kernels it replaces (nodes, zero rows and edge list, scan, packing,
 // walks, max-flow: six launches): 32 GPUs x 65,536 64.6 -> 23.9 us, 64 GPUs x 262,144 725 -> 243 us,
-// 8 GPUs x 256 24 -> 8 us.  What bounds it: the walks' binary64 divisions, then the stores of the rows.  (The asymmetric split stays with kv_kernel: every lane of a group would recompute the
-// stages' layer counts, which measured twice as slow.)
+// 8 GPUs x 256 24 -> 8 us.  What bounds it: the walks' binary64
+// divisions, then the stores of the rows.  (The asymmetric split stays with kv_kernel: every lane
+// of a group would recompute the stages' layer counts, which measured twice as slow.)
 constexpr int kWalkLanes = 4;
 constexpr int kNetBlock = 256;
 constexpr int kNetWaves = kNetBlock / 64;
