@@ -51,9 +51,8 @@ FP64_VALU_PEAK_GOPS = 256 * 4 * 16 * 2.4
 # taken on (first 16 hex digits of the source file's SHA-256); otherwise traffic is null.
 COUNTER_SCALE = {"fetch": 2.0, "write": 1.0}
 KERNEL_TRAFFIC = {
-    # workload 3 (profiles/all_kernels_workload3.md); kv the listed path's four kernels (rows,
-    # scan, packing, walks), maxflow the instantiation with the folded argmax, best the final
-    # reduction of its slots
+    # workload 3 (profiles/all_kernels_workload3.md); taken on the six-launch network path
+    # that the fused network kernel replaced: the hashes differ, so no traffic is reported from it
     3: {
         "setup": {"source_sha256_16": "cfe308a8f566cbcf", "fetch_kib": 70.55, "write_kib": 57.43},
         "decode": {"source_sha256_16": "cfe308a8f566cbcf", "fetch_kib": 1714, "write_kib": 2.884e+04},
