@@ -681,6 +681,7 @@ __device__ __forceinline__ uint32_t set_nib(uint32_t v, int i, int x) {
 // 1.32 ms at 32 GPUs x 16,384 candidates; whole calls with 64 and 8: 3.64 and 2.44 ms at x 65,536, 5.59
 // and 1.95 ms at 64 GPUs x 4,096.
 constexpr int kOrderLanes = 8;
+constexpr int64_t kOrderGrid = 1 << 22;  // workgroups of a launch in x, at most
 constexpr int kOrderThreads = 256;  // kv_order_kernel: wave 0 holds the lanes, all four waves search
 constexpr int kOrderLevels = 4;     // search levels below a queued prefix, at most
 constexpr int kOrderQueue = 2 * kOrderThreads;  // prefixes handed out per edge, at least (when nx allows)
@@ -819,16 +820,20 @@ __device__ __forceinline__ void order_search(OrderShared& S, int nx, int ny, int
 // (shared in LDS, starting from the ascending time).  The search ends once the best reaches a
 // bound below every order pair (pairs_bound, the largest over the threads).  The minimum is the
 // one the enumeration of every order pair finds.  Per-replica granularity.
+//
+// The lanes cover the first `rows` KV rows of every candidate, kOrderLanes a workgroup, over a grid of
+// kOrderGrid workgroups a row of y: HIP takes less than 2^32 threads in a dimension, which a grid of one
+// dimension would reach at 2^27 (edge, candidate) cells.
 template <int W>
-__global__ void __launch_bounds__(kOrderThreads) kv_order_kernel(Problem p, CostOut o, FlowNet f) {
+__global__ void __launch_bounds__(kOrderThreads) kv_order_kernel(Problem p, CostOut o, FlowNet f, int rows) {
     extern __shared__ __attribute__((aligned(16))) uint8_t sm[];
     OrderShared& S = *reinterpret_cast<OrderShared*>(sm);
     uint8_t* mem = sm + kOrderLds;
     const int tid = threadIdx.x;
     const int stride = kOrderLanes;
-    const int64_t gid = (int64_t)blockIdx.x * kOrderLanes + tid;
+    const int64_t gid = ((int64_t)blockIdx.y * kOrderGrid + blockIdx.x) * kOrderLanes + tid;
     const int64_t N = p.N;
-    bool live = tid < kOrderLanes && gid < (int64_t)f.max_pd * N;
+    bool live = tid < kOrderLanes && gid < (int64_t)rows * N;
     const int e = live ? (int)(gid / N) : 0;
     const int n = live ? (int)(gid - (int64_t)e * N) : 0;
     const int np = live ? f.n_p[n] : 0, nd = live ? f.n_d[n] : 0;
@@ -1590,13 +1595,12 @@ hipError_t launch_w(const Problem& p, const CostOut& o, const FlowNet& f, hipStr
     prof_mark(kKNodes, false, s);
     launch_nodes<W>(p, o, f, s);
     prof_mark(kKNodes, true, s);
-    const int64_t lanes = (int64_t)f.max_pd * p.N;
-    const int blocks = (int)((lanes + kOrderLanes - 1) / kOrderLanes);
-    // kv_kernel: a grid row per KV row a replica network can have (its n_p + n_d <= Kmax nodes
-    // give at most floor(Kmax/2) ceil(Kmax/2) <= 16,256 rows, within the grid's y limit)
-    const int64_t rows_pd = (int64_t)(p.Kmax / 2) * ((p.Kmax + 1) / 2);
-    const dim3 grid_kv((unsigned)((p.N + kKvBlock - 1) / kKvBlock),
-                       (unsigned)(f.max_pd < rows_pd ? f.max_pd : rows_pd));
+    // the KV rows a replica network can have, whatever room the arrays have: its n_p + n_d <= Kmax nodes
+    // give at most floor(Kmax/2) ceil(Kmax/2) <= 16,256 (within the grid's y limit); a launch has one row
+    // at least
+    const int rows_pd = (p.Kmax / 2) * ((p.Kmax + 1) / 2);
+    const int rows = rows_pd < 1 ? 1 : (f.max_pd < rows_pd ? f.max_pd : rows_pd);
+    const dim3 grid_kv((unsigned)((p.N + kKvBlock - 1) / kKvBlock), (unsigned)rows);  // kv_kernel: a grid row per KV row
     const size_t lds = 2 * (size_t)p.G * kKvBlock;
     prof_mark(kKKv, false, s);
     if (p.granularity != 0) {
@@ -1608,8 +1612,10 @@ hipError_t launch_w(const Problem& p, const CostOut& o, const FlowNet& f, hipStr
             e = table ? launch_kv_gpu<W, false, true>(p, f, o, s) : launch_kv_gpu<W, false, false>(p, f, o, s);
         if (e != hipSuccess) return e;
     } else if (p.variant & HX_VARIANT_KV_ORDER) {
-        hipLaunchKernelGGL(kv_order_kernel<W>, dim3(blocks), dim3(kOrderThreads),
-                           kOrderLds + 2 * (size_t)p.G * kOrderLanes, s, p, o, f);
+        const int64_t wgs = ((int64_t)rows * p.N + kOrderLanes - 1) / kOrderLanes;
+        const dim3 grid((unsigned)(wgs < kOrderGrid ? wgs : kOrderGrid), (unsigned)((wgs + kOrderGrid - 1) / kOrderGrid));
+        hipLaunchKernelGGL(kv_order_kernel<W>, grid, dim3(kOrderThreads), kOrderLds + 2 * (size_t)p.G * kOrderLanes, s, p,
+                           o, f, rows);
     } else if (p.variant & HX_VARIANT_ASYM) {
         hipLaunchKernelGGL((kv_kernel<W, true, false>), grid_kv, dim3(kKvBlock), lds + sizeof(double) * p.G, s, p,
                            o, f);

@@ -111,6 +111,48 @@ def test_kv_order_parity(torch, cfg, n, variant):
     assert (fn["kv_cap"][upd] >= asc["kv_cap"][upd]).all()
 
 
+@pytest.mark.parametrize("tiles,spare", [(256, 1), (257, 1), (3, 5)])
+def test_kv_order_large_grids(torch, tiles, spare):
+    """The stage-order search over more (edge, candidate) cells than one launch has lanes for: 2,048
+    candidates of workload 4 (256 KV rows) repeated 256 times are 2^27 cells, 257 times more than that,
+    with the arrays' own rows; and arrays with five times the rows a network can have.  Every repetition's
+    KV rows, flow values and the best equal those of the 2,048 candidates alone."""
+    n = 2048
+    prob = dataclasses.replace(I.make_problem(4, n_cand=n), variant=ORDER)
+    dp = hx.DeviceProblem.upload(prob)
+    one = hx.Workspace.for_problem(dp)
+    hx.score_batch(dp, one)
+    many = dp.with_candidates(dp.tensors["assign"].repeat(1, tiles), dp.tensors["role"].repeat(1, tiles))
+    ws = hx.Workspace.for_problem(many)
+    mp, md, mpd = ws.net.dims
+    ws.net = hx.FlowNetBuffers.empty((mp, md, mpd * spare), n * tiles, fill=-1)
+    say(f"KV stage-order search: {mpd * spare} rows x {n * tiles} candidates")
+    hx.score_batch(many, ws)
+    torch.cuda.synchronize()
+    used = torch.arange(mpd, device="cuda")[:, None] < (one.net.n_p * one.net.n_d)[None, :]
+    kv = ws.net.kv_cap.view(mpd * spare, tiles, n)
+    for i in range(tiles):
+        assert bool((~used | (kv[:mpd, i] == one.net.kv_cap)).all()), f"repetition {i}"
+    assert bool((kv[mpd:] == -1).all())
+    assert bool((ws.flow_value.view(tiles, n) == one.flow_value).all())
+    assert ws.best.tolist() == one.best.tolist()
+
+
+def test_kv_order_single_slot(torch):
+    """One group slot: networks that have no KV row."""
+    a, r = I.placement_from_groups([list(range(8))], [I.PREFILL], 8, 1)
+    for variant in (0, ORDER):
+        prob = dataclasses.replace(Hh.problem(Hh.cluster_c1(), Hh.MODELS["opt30b"], a, r), variant=variant)
+        dp = hx.DeviceProblem.upload(prob)
+        ws = hx.Workspace.for_problem(dp)
+        ws.net = hx.FlowNetBuffers.empty((1, 1, 1), 1, fill=-1)
+        for call in (hx.score, hx.score_batch):
+            call(dp, ws)
+            torch.cuda.synchronize()
+            assert (ws.net.n_p.tolist(), ws.net.n_d.tolist(), ws.net.kv_cap.tolist()) == ([1], [0], [[-1]])
+            assert ws.flow_value.tolist() == [0] and ws.best.tolist() == [0, 0]
+
+
 @pytest.mark.parametrize("dpp", [8, 4])
 def test_kv_order_deep_hidden_pairing(torch, dpp):
     """Eight one-GPU prefill stages against eight or four one-GPU decode stages whose fast links
