@@ -385,7 +385,7 @@ int hx_gather_candidates(int32_t n_gpus, const hx_candidates *src, const int32_t
  * bound keeps every cut of up to 255 GPUs below 2^62), node weights the memory limits in whole
  * bytes, so cuts, gains and their sums are exact 64-bit integer sums. */
 
-/* Device scratch both calls need (an [n_gpus][n_gpus] int64 weight table they fill first, and a flag);
+/* Device scratch both calls need (an [n_gpus][n_gpus] int64 weight table they fill first);
  * 0 for n_gpus outside [2, 255]. */
 size_t hx_partition_workspace_bytes(int32_t n_gpus);
 

@@ -485,7 +485,7 @@ int hx_guided_moves(int32_t n_gpus, int32_t granularity, const hx_candidates* pa
 
 size_t hx_partition_workspace_bytes(int32_t n_gpus) {
     if (n_gpus < 2 || n_gpus > HX_MAX_GPUS) return 0;
-    return ((size_t)n_gpus * n_gpus * sizeof(int64_t) + sizeof(int64_t) + 255) & ~(size_t)255;  // and a flag
+    return ((size_t)n_gpus * n_gpus * sizeof(int64_t) + 255) & ~(size_t)255;
 }
 
 int hx_spectral_order(const hx_cluster* cluster, int32_t iters, void* workspace, size_t workspace_bytes,

@@ -263,7 +263,7 @@ __host__ __device__ inline size_t pg_lds_bytes(int G) { return (size_t)G * kPgMa
 // A pair's key is 2^16 gain + (2^16 - 1 - pair) as a binary64 integer, so that one maximum picks the
 // largest gain and, on ties, the lowest pair.  All values are whole numbers held exactly, which needs
 // a row of weights below 2^29 MB/s and memories below 2^52 in all: graphs past these (links of 16 TB/s
-// at 32 GPUs, 2 TB/s at 255) are left to partition_kernel, which holds them as 64-bit integers (flag).
+// at 32 GPUs, 2 TB/s at 255) are left to partition_kernel, which holds them as 64-bit integers.
 //
 // The pairs are laid out as (a, a + s mod G), s = 1 .. G/2: lane a of a set of P lanes holds node a's
 // state, and the NT / P sets take every (NT / P)-th shift s.  A node's partner is then at a constant
@@ -339,7 +339,7 @@ constexpr double kPgNone = -4611686018427387904.0;  // -2^62: below every key
 
 // kLdsW: the weights staged in LDS as 32-bit integers.
 template <int P, bool kLdsW>
-__global__ void __launch_bounds__(PgShape<P>::kBlock) partition_gain_kernel(PgArgs a, int Kh, int32_t* flag) {
+__global__ void __launch_bounds__(PgShape<P>::kBlock) partition_gain_kernel(PgArgs a, int Kh) {
     using Sh = PgShape<P>;
     constexpr int kNT = Sh::kNT, kSub = Sh::kSub, kSlots = Sh::kSlots;
     extern __shared__ __attribute__((aligned(16))) unsigned char pg_sm[];
@@ -382,7 +382,9 @@ __global__ void __launch_bounds__(PgShape<P>::kBlock) partition_gain_kernel(PgAr
         if (sub == 0) memd[x] = mx;
     }
     bad = __syncthreads_or(bad) != 0;
-    if (blockIdx.x == 0 && threadIdx.x == 0) *flag = bad ? 1 : 0;
+    // a candidate left to partition_kernel is marked in its assignment: GPU 0 unused (its group is 0 in
+    // every partition)
+    if (bad && n < N && tid == 0) a.assign[n] = HX_UNUSED;
     if (bad || n >= N) return;  // wavefronts of their own candidates, or the whole workgroup
     auto weight = [&](int u, int v) -> int32_t {
         return kLdsW ? wl[u * G + v] : (int32_t)a.w[(int64_t)u * G + v];
@@ -590,8 +592,8 @@ __global__ void __launch_bounds__(PgShape<P>::kBlock) partition_gain_kernel(PgAr
 }
 
 // Any graph, in 64-bit integers; a workgroup takes every gridDim.x-th candidate.  Only graphs past the
-// exact ranges of partition_gain_kernel, which says so in flag, are partitioned here.
-__global__ void __launch_bounds__(kPgBlock) partition_kernel(PgArgs a, const int32_t* flag) {
+// exact ranges of partition_gain_kernel, which marks their candidates, are partitioned here.
+__global__ void __launch_bounds__(kPgBlock) partition_kernel(PgArgs a) {
     extern __shared__ __attribute__((aligned(16))) unsigned char pg_sm[];
     long long* gval = reinterpret_cast<long long*>(pg_sm);  // [G][kPgMaxK]
     __shared__ long long memv[kPgBlock];
@@ -607,8 +609,8 @@ __global__ void __launch_bounds__(kPgBlock) partition_kernel(PgArgs a, const int
     const int tid = threadIdx.x;
     const int G = a.G;
     const int64_t N = a.N;
-    if (*flag == 0) return;  // uniform
     for (int n = blockIdx.x; n < N; n += gridDim.x) {
+    if (a.assign[n] != HX_UNUSED) return;  // uniform: none is marked, or all are
     const uint64_t r = a.rnd[n];
     if (tid < G) {
         const int t = a.gpu_type[tid];
@@ -788,7 +790,7 @@ hipError_t launch_spectral(int32_t G, const double* beta, int64_t* w, int32_t it
 }
 
 template <int P, bool kLdsW>
-static hipError_t launch_gain(const PgArgs& a, int Kh, int32_t* flag, hipStream_t s) {
+static hipError_t launch_gain(const PgArgs& a, int Kh, hipStream_t s) {
     using Sh = PgShape<P>;
     const size_t lds = (kLdsW ? (sizeof(int32_t) * (size_t)a.G * a.G + 15) & ~(size_t)15 : 0) +
                        Sh::kPer * pg_fast_lds(a.G, Kh);
@@ -798,7 +800,7 @@ static hipError_t launch_gain(const PgArgs& a, int Kh, int32_t* flag, hipStream_
         if (e != hipSuccess) return e;
     }
     hipLaunchKernelGGL((partition_gain_kernel<P, kLdsW>), dim3((unsigned)((a.N + Sh::kPer - 1) / Sh::kPer)), dim3(Sh::kBlock), lds,
-                       s, a, Kh, flag);
+                       s, a, Kh);
     return hipGetLastError();
 }
 
@@ -808,19 +810,17 @@ hipError_t launch_partition(const Problem& p, int64_t* w, const int32_t* order, 
     hipLaunchKernelGGL(graph_kernel, dim3((unsigned)((cells + 255) / 256)), dim3(256), 0, s, p.G, p.beta, w);
     PgArgs a{p.G, p.Kmax, p.N, p.L, p.H, p.Hkv, p.B, p.s_in, p.s_out, w, order, p.gpu_type, p.mem, p.T, rnd,
              assign, role};
-    // the word after the weights: whether the graph is past the exact ranges of the incremental kernel
-    int32_t* flag = reinterpret_cast<int32_t*>(w + cells);
     int Kh = p.Kmax < p.G ? p.Kmax : p.G;
     if (Kh > kPgMaxK) Kh = kPgMaxK;
     if (Kh < 2) Kh = 2;
     prof_mark(kKPartition, false, s);
     hipError_t e;
-    if (p.G <= 32) e = launch_gain<32, true>(a, Kh, flag, s);
-    else if (p.G <= 64) e = launch_gain<64, true>(a, Kh, flag, s);
+    if (p.G <= 32) e = launch_gain<32, true>(a, Kh, s);
+    else if (p.G <= 64) e = launch_gain<64, true>(a, Kh, s);
     // above 104 GPUs the staged weights would leave a CU one workgroup (more than 80 KB of LDS)
-    else if (p.G <= 104) e = launch_gain<128, true>(a, Kh, flag, s);
-    else if (p.G <= 128) e = launch_gain<128, false>(a, Kh, flag, s);
-    else e = launch_gain<256, false>(a, Kh, flag, s);
+    else if (p.G <= 104) e = launch_gain<128, true>(a, Kh, s);
+    else if (p.G <= 128) e = launch_gain<128, false>(a, Kh, s);
+    else e = launch_gain<256, false>(a, Kh, s);
     if (e != hipSuccess) return e;
     // gval of 255 GPUs (65,280 bytes) takes the workgroup past 64 KB of LDS, which gfx950 allows
     // (160 KB per workgroup) once the kernel's dynamic limit is raised
@@ -830,7 +830,7 @@ hipError_t launch_partition(const Problem& p, int64_t* w, const int32_t* order, 
                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) return e;
     }
-    hipLaunchKernelGGL(partition_kernel, dim3((unsigned)(p.N < 512 ? p.N : 512)), dim3(kPgBlock), lds, s, a, flag);
+    hipLaunchKernelGGL(partition_kernel, dim3((unsigned)(p.N < 512 ? p.N : 512)), dim3(kPgBlock), lds, s, a);
     prof_mark(kKPartition, true, s);
     return hipGetLastError();
 }

@@ -120,6 +120,35 @@ def test_partition_large_weights(torch):
     assert np.array_equal(role.cpu().numpy(), want_r)
 
 
+@pytest.mark.parametrize("gpus,links", [(8, 1.0), (8, 2e4), (15, 1.0), (32, 2e4)])
+def test_partition_workspace_is_the_weight_table(torch, gpus, links):
+    """The workspace is the [G][G] int64 weight table, rounded up to 256 bytes, and nothing past it is written."""
+    size = (gpus * gpus * 8 + 255) & ~255
+    assert hx.lib().hx_partition_workspace_bytes(gpus) == size
+    prob = I.make_problem(2, n_cand=1)
+    tab = np.array([I.GPU_TYPES["A"]])
+    cl = I.cluster_from_nodes(np.zeros(gpus, np.int32), tab, np.full(((gpus + 3) // 4,) * 2, 12.5e9))
+    cl = dataclasses.replace(cl, beta=np.ascontiguousarray(cl.beta * links))
+    blank = lambda rows: np.full((rows, 1), I.UNUSED, np.uint8)
+    prob = dataclasses.replace(prob, cluster=cl, max_groups=4, assign=blank(gpus), role=blank(4))
+    buf = torch.full((size + 4096,), 0x5A, dtype=torch.uint8, device="cuda")
+    ws, n = buf[:size], 70
+    dp = hx.DeviceProblem.upload(prob)
+    order = torch.empty(gpus, dtype=torch.int32, device="cuda")
+    say(f"partition workspace: {gpus} GPUs, links x {links}")
+    hx.spectral_order(dp, ws, order, iters=60)
+    rnd_h = I.partition_draws(2, n)
+    rnd = torch.as_tensor(rnd_h.view(np.int64)).to("cuda")
+    assign = torch.empty((gpus, n), dtype=torch.uint8, device="cuda")
+    role = torch.empty((4, n), dtype=torch.uint8, device="cuda")
+    hx.partition_candidates(dp, ws, order, rnd, assign, role)
+    torch.cuda.synchronize()
+    assert bool((buf[size:] == 0x5A).all())
+    want_a, want_r = hxo.partition_candidates(prob, hxo.spectral_order(prob, 60)[0], rnd_h)
+    assert np.array_equal(assign.cpu().numpy(), want_a)
+    assert np.array_equal(role.cpu().numpy(), want_r)
+
+
 @pytest.mark.parametrize("gpus,groups,n,ties,links", [
     (2, 2, 9, False, 1.0), (3, 1, 9, False, 1.0), (15, 4, 33, True, 1.0), (31, 32, 40, False, 1.0), (32, 16, 257, True, 1.0),
     (33, 32, 40, False, 1.0), (49, 9, 21, True, 1.0), (64, 32, 30, True, 1.0), (65, 8, 12, False, 1.0), (81, 32, 6, False, 1.0),
