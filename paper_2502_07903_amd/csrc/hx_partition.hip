@@ -591,9 +591,8 @@ __global__ void __launch_bounds__(PgShape<P>::kBlock) partition_gain_kernel(PgAr
     if (sub == 0 && x < G) a.assign[(int64_t)x * N + n] = (uint8_t)gx;
 }
 
-// Any graph, in 64-bit integers; a workgroup takes every gridDim.x-th candidate.  Only graphs past the
-// exact ranges of partition_gain_kernel, which marks their candidates, are partitioned here.
-__global__ void __launch_bounds__(kPgBlock) partition_kernel(PgArgs a) {
+// Candidate n of any graph, in 64-bit integers, by a workgroup (lane tid).
+__device__ __forceinline__ void partition_one(const PgArgs& a, int G, int tid, int n) {
     extern __shared__ __attribute__((aligned(16))) unsigned char pg_sm[];
     long long* gval = reinterpret_cast<long long*>(pg_sm);  // [G][kPgMaxK]
     __shared__ long long memv[kPgBlock];
@@ -606,11 +605,7 @@ __global__ void __launch_bounds__(kPgBlock) partition_kernel(PgArgs a) {
     __shared__ int first[kPgMaxK], newid[kPgMaxK], side[kPgMaxK];
     __shared__ long long sw[kPgMaxK * kPgMaxK];
     __shared__ long long cum[kPgBlock];
-    const int tid = threadIdx.x;
-    const int G = a.G;
     const int64_t N = a.N;
-    for (int n = blockIdx.x; n < N; n += gridDim.x) {
-    if (a.assign[n] != HX_UNUSED) return;  // uniform: none is marked, or all are
     const uint64_t r = a.rnd[n];
     if (tid < G) {
         const int t = a.gpu_type[tid];
@@ -772,7 +767,25 @@ __global__ void __launch_bounds__(kPgBlock) partition_kernel(PgArgs a) {
     if (tid < G) a.assign[(int64_t)tid * N + n] = (uint8_t)grp[tid];
     for (int k = tid; k < a.Kmax; k += kPgBlock)
         a.role[(int64_t)k * N + n] = k < used ? (uint8_t)(side[k] ? HX_DECODE : HX_PREFILL) : (uint8_t)HX_UNUSED;
-    __syncthreads();  // the next candidate reuses the LDS
+}
+
+// The candidates that partition_gain_kernel left marked (all or none), a workgroup every gridDim.x-th one.
+// kPgGrid workgroups are several times what the chip holds at once (24 KB of LDS each at 32 GPUs), so that
+// those that end early are replaced, and few enough to cost a call with none marked 3 us at most (a
+// workgroup per candidate: 20 us at 8 GPUs x 100,000).  G and the lane are hidden from the compiler, which
+// would otherwise keep what it derives from them in registers across candidates (93 instead of 72).
+// Calls past the ranges with this kernel alone, a workgroup per candidate / with 512 workgroups / now:
+// 16 GPUs x 16,384 406 / 1,058 / 432 us (18 of them the gain kernel's), 32 x 16,384 1,770 / 4,409 / 1,784,
+// 64 x 2,048 2,250 / 3,740 / 2,200, 100 x 1,000 7.2 / 8.8 / 7.2 ms, 255 x 600 117 / 153 / 118 ms; with
+// 4,096 workgroups 489 us and 2,020 us at the first two.
+constexpr int kPgGrid = 16384;
+__global__ void __launch_bounds__(kPgBlock) partition_kernel(PgArgs a) {
+    for (int64_t n = blockIdx.x; n < a.N; n += gridDim.x) {
+        if (a.assign[n] != HX_UNUSED) return;  // uniform
+        int G = a.G, tid = threadIdx.x;
+        asm volatile("" : "+s"(G), "+v"(tid));
+        partition_one(a, G, tid, (int)n);
+        __syncthreads();  // the next candidate reuses the LDS
     }
 }
 
@@ -830,7 +843,7 @@ hipError_t launch_partition(const Problem& p, int64_t* w, const int32_t* order, 
                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) return e;
     }
-    hipLaunchKernelGGL(partition_kernel, dim3((unsigned)(p.N < 512 ? p.N : 512)), dim3(kPgBlock), lds, s, a);
+    hipLaunchKernelGGL(partition_kernel, dim3((unsigned)(p.N < kPgGrid ? p.N : kPgGrid)), dim3(kPgBlock), lds, s, a);
     prof_mark(kKPartition, true, s);
     return hipGetLastError();
 }
