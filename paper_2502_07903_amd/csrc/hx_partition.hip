@@ -335,6 +335,10 @@ __device__ __forceinline__ void pg_sync() {
     }
 }
 
+// Workgroups of a grid row: HIP takes less than 2^32 threads in a dimension, which 2^22 workgroups of 1,024
+// lanes would reach (partition_kernel alone took 2^24 candidates).
+constexpr int64_t kPgGridX = 1 << 21;
+
 constexpr double kPgNone = -4611686018427387904.0;  // -2^62: below every key
 
 // kLdsW: the weights staged in LDS as 32-bit integers.
@@ -347,7 +351,7 @@ __global__ void __launch_bounds__(PgShape<P>::kBlock) partition_gain_kernel(PgAr
     const int G = a.G, tid = threadIdx.x % kNT, cand = threadIdx.x / kNT;
     const int x = tid % P, sub = tid / P, lane = threadIdx.x & 63;
     const int64_t N = a.N;
-    const int64_t n = (int64_t)blockIdx.x * Sh::kPer + cand;
+    const int64_t n = ((int64_t)blockIdx.y * kPgGridX + blockIdx.x) * Sh::kPer + cand;
     int32_t* wl = reinterpret_cast<int32_t*>(pg_sm);  // kLdsW: [G][G]
     const size_t wbytes = kLdsW ? (sizeof(int32_t) * (size_t)G * G + 15) & ~(size_t)15 : 0;
     unsigned char* base = pg_sm + wbytes + cand * pg_fast_lds(G, Kh);
@@ -812,8 +816,9 @@ static hipError_t launch_gain(const PgArgs& a, int Kh, hipStream_t s) {
                                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) return e;
     }
-    hipLaunchKernelGGL((partition_gain_kernel<P, kLdsW>), dim3((unsigned)((a.N + Sh::kPer - 1) / Sh::kPer)), dim3(Sh::kBlock), lds,
-                       s, a, Kh);
+    const int64_t wgs = ((int64_t)a.N + Sh::kPer - 1) / Sh::kPer;
+    const dim3 grid((unsigned)(wgs < kPgGridX ? wgs : kPgGridX), (unsigned)((wgs + kPgGridX - 1) / kPgGridX));
+    hipLaunchKernelGGL((partition_gain_kernel<P, kLdsW>), grid, dim3(Sh::kBlock), lds, s, a, Kh);
     return hipGetLastError();
 }
 

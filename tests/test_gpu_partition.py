@@ -185,3 +185,27 @@ def test_partition_sizes(torch, gpus, groups, n, ties, links):
     want_a, want_r = hxo.partition_candidates(prob, want_o, rnd_h)
     assert np.array_equal(assign.cpu().numpy(), want_a)
     assert np.array_equal(role.cpu().numpy(), want_r)
+
+
+def test_partition_many_candidates(torch):
+    """More candidates than one grid row of 1,024-lane workgroups can hold (2^22): memories of 0 leave
+    every GPU in group 0, so each candidate takes no swap.  Every repetition of 4,099 draws equals the
+    oracle's."""
+    G, K, part, tiles = 129, 2, 4099, 1024
+    cl = I.cluster_from_nodes(np.zeros(G, np.int32), np.array([I.GPU_TYPES["A"]]), np.full(((G + 3) // 4,) * 2, 12.5e9))
+    cl = dataclasses.replace(cl, type_mem=np.zeros(1))
+    blank = lambda rows: np.full((rows, 1), I.UNUSED, np.uint8)
+    prob = I.Problem(cl, dict(I.LLAMA2_70B), 1500.0, 400.0, I._mask((1, 2, 4, 8)), I._mask(range(1, 9)), 0, K, blank(G), blank(K))
+    dp = hx.DeviceProblem.upload(prob)
+    ws = hx.partition_workspace(dp)
+    order = torch.arange(G, dtype=torch.int32, device="cuda")
+    rnd_h = np.random.default_rng(9).integers(0, 2**64, part, dtype=np.uint64)
+    rnd = torch.as_tensor(rnd_h.view(np.int64)).to("cuda").repeat(tiles)
+    assign = torch.full((G, part * tiles), 0xEE, dtype=torch.uint8, device="cuda")
+    role = torch.full((K, part * tiles), 0xEE, dtype=torch.uint8, device="cuda")
+    say(f"partition: {G} GPUs, N={part * tiles}")
+    hx.partition_candidates(dp, ws, order, rnd, assign, role)
+    torch.cuda.synchronize()
+    want_a, want_r = hxo.partition_candidates(prob, np.arange(G, dtype=np.int32), rnd_h)
+    assert bool((assign.view(G, tiles, part) == torch.as_tensor(want_a).cuda()[:, None, :]).all())
+    assert bool((role.view(K, tiles, part) == torch.as_tensor(want_r).cuda()[:, None, :]).all())
