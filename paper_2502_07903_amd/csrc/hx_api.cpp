@@ -415,15 +415,15 @@ int hx_score_batch(const hx_cluster* cluster, hx_model model, hx_workload wl, hx
     const hx::Problem p = make_problem(cluster, model, wl, space, cand);
     const hx::FlowNet f = make_net(net);
     // the link table and the list follow the cost model's scratch, the argmax's area follows them:
-    // per-workgroup winners for the per-GPU path, otherwise the fused argmax's slots and the list
-    // count and ticket of the replica path (all zeroed by the cost model's first kernel)
+    // per-workgroup winners for the per-GPU path, otherwise the fused argmax's slots with the list count
+    // and tickets of the replica path (all zeroed by the cost model's first kernel)
     const size_t off_mid =
         (hx::cost_workspace_bytes(cluster->n_gpus, cand->max_groups, cand->n_cand) + 255) & ~(size_t)255;
     const size_t off_part = off_mid + score_mid_bytes(cluster->n_gpus, cand->n_cand);
     unsigned char* part = static_cast<unsigned char*>(workspace) + off_part;
     const bool direct = hx::flownet_values_direct(p) && hx::maxflow_workgroup_plan(net->max_p, net->max_d, net->max_pd);
     unsigned long long* slots = direct ? nullptr : reinterpret_cast<unsigned long long*>(part);
-    hipError_t e = hx::launch_cost(p, make_cost(cost), workspace, stream, slots, direct ? 0 : hx::kArgSlots + 1);
+    hipError_t e = hx::launch_cost(p, make_cost(cost), workspace, stream, slots, direct ? 0 : hx::kNetArea);
     if (e == hipSuccess) {
         if (direct) {
             void* table = static_cast<unsigned char*>(workspace) + off_mid;
@@ -432,10 +432,8 @@ int hx_score_batch(const hx_cluster* cluster, hx_model model, hx_workload wl, hx
             if (e == hipSuccess) e = hx::launch_maxflow_listed(f, flow_value, round_budget(), count + 16, count, stream);
         } else if (hx::score_net_fits(p)) {
             int32_t* list = reinterpret_cast<int32_t*>(static_cast<unsigned char*>(workspace) + off_mid);
-            int32_t* words = reinterpret_cast<int32_t*>(slots + hx::kArgSlots);
-            e = hx::launch_score_net(p, make_cost(cost), f, flow_value, slots, words, list, stream);
-            if (e == hipSuccess)
-                e = hx::launch_finish(p, f, flow_value, round_budget(), slots, words, list, words + 1, best, stream);
+            e = hx::launch_score_net(p, make_cost(cost), f, flow_value, slots, list, stream);
+            if (e == hipSuccess) e = hx::launch_finish(p, f, flow_value, round_budget(), slots, list, best, stream);
             return e == hipSuccess ? HX_OK : hip_error(e);
         } else {
             e = hx::launch_flownet(p, make_cost(cost), f, stream);

@@ -191,7 +191,8 @@ hipError_t launch_best(const int32_t* flow_value, int32_t n, int32_t* best, hipS
     return hipGetLastError();
 }
 
-size_t best_parts_bytes() { return sizeof(uint64_t) * (kPartMax > kArgSlots + 1 ? kPartMax : kArgSlots + 1); }
+static_assert(kNetArea >= kPartMax && kNetArea >= kArgSlots, "the argmax's area holds every path's words");
+size_t best_parts_bytes() { return sizeof(uint64_t) * kNetArea; }
 
 hipError_t launch_best_parts(const int32_t* flow_value, int32_t n, int32_t* best, int32_t* counter, uint64_t* part,
                              hipStream_t s) {

@@ -1253,7 +1253,7 @@ __device__ __forceinline__ int nth_bit(uint32_t m, int i) {
 
 template <int W, bool kCls, int C>
 __global__ void __launch_bounds__(kNetBlock) net_kernel(Problem p, CostOut o, FlowNet f, int32_t* flow_value,
-                                                        unsigned long long* arg, int32_t* list_count, int32_t* list) {
+                                                        unsigned long long* area, int32_t* list) {
     static_assert(64 % C == 0 && C >= kNetWaves, "a wavefront holds whole sets of candidates");
     constexpr int kGroups = 64 / kWalkLanes;
     constexpr int kParts = kNetBlock / C;                              // lanes that share a candidate's slots and rows
@@ -1432,11 +1432,11 @@ __global__ void __launch_bounds__(kNetBlock) net_kernel(Problem p, CostOut o, Fl
     const uint64_t bal = __ballot(own && left);
     if (bal) {
         int32_t at = 0;
-        if (lane == 0) at = atomicAdd(list_count, (int32_t)__popcll(bal));
+        if (lane == 0) at = atomicAdd(net_list_count(area), (int32_t)__popcll(bal));
         at = __shfl(at, 0, 64);
         if (own && left) list[at + __popcll(bal & ((1ull << lane) - 1))] = (int32_t)n;
     }
-    fold_argmax(own && !left ? argmax_key(v, (int32_t)n) : 0ull, arg);
+    fold_argmax<kNetSlots>(own && !left ? argmax_key(v, (int32_t)n) : 0ull, area);
 }
 
 // Per-GPU nodes: one workgroup of kGpuKvWaves wavefronts per 64 candidates (a lane per
@@ -1665,39 +1665,39 @@ bool score_net_fits(const Problem& p) {
 
 template <int W, bool kCls, int C>
 static void launch_net_c(const Problem& p, const CostOut& o, const FlowNet& f, int32_t* flow_value,
-                         unsigned long long* slots, int32_t* list_count, int32_t* list, hipStream_t s) {
+                         unsigned long long* area, int32_t* list, hipStream_t s) {
     const int64_t tiles = ((int64_t)p.N + C - 1) / C;
     hipLaunchKernelGGL((net_kernel<W, kCls, C>), dim3((unsigned)(8 * ((tiles + 7) / 8))), dim3(kNetBlock),
-                       net_lds<C>(p.G), s, p, o, f, flow_value, slots, list_count, list);
+                       net_lds<C>(p.G), s, p, o, f, flow_value, area, list);
 }
 
 template <int W, bool kCls>
 static void launch_net(const Problem& p, const CostOut& o, const FlowNet& f, int32_t* flow_value,
-                       unsigned long long* slots, int32_t* list_count, int32_t* list, hipStream_t s) {
+                       unsigned long long* area, int32_t* list, hipStream_t s) {
     // Candidates per workgroup: the fewest of 16, 32, 64 that need at most 1,024 workgroups (four
     // per CU, 16 wavefronts), so that small batches still spread over the chip, and 64 beyond.
     // Measured: 16 GPUs x 4,096 candidates 9.3 us with 16 against 18.2 with 64; 27 GPUs x 10,007
     // with many feasible edges 27.6 against 49.7; 32 GPUs x 65,536 43.8 against 23.4 (28.8 with 32).
     if (p.N <= 16 * 1024)
-        launch_net_c<W, kCls, 16>(p, o, f, flow_value, slots, list_count, list, s);
+        launch_net_c<W, kCls, 16>(p, o, f, flow_value, area, list, s);
     else if (p.N <= 32 * 1024)
-        launch_net_c<W, kCls, 32>(p, o, f, flow_value, slots, list_count, list, s);
+        launch_net_c<W, kCls, 32>(p, o, f, flow_value, area, list, s);
     else
-        launch_net_c<W, kCls, 64>(p, o, f, flow_value, slots, list_count, list, s);
+        launch_net_c<W, kCls, 64>(p, o, f, flow_value, area, list, s);
 }
 
 hipError_t launch_score_net(const Problem& p, const CostOut& o, const FlowNet& f, int32_t* flow_value,
-                            unsigned long long* slots, int32_t* list_count, int32_t* list, hipStream_t s) {
+                            unsigned long long* area, int32_t* list, hipStream_t s) {
     prof_mark(kKKv, false, s);
     const int W = mask_words(p.G);
     if (p.n_cls > 0) {
-        if (W == 1) launch_net<1, true>(p, o, f, flow_value, slots, list_count, list, s);
-        else if (W == 2) launch_net<2, true>(p, o, f, flow_value, slots, list_count, list, s);
-        else launch_net<4, true>(p, o, f, flow_value, slots, list_count, list, s);
+        if (W == 1) launch_net<1, true>(p, o, f, flow_value, area, list, s);
+        else if (W == 2) launch_net<2, true>(p, o, f, flow_value, area, list, s);
+        else launch_net<4, true>(p, o, f, flow_value, area, list, s);
     } else {
-        if (W == 1) launch_net<1, false>(p, o, f, flow_value, slots, list_count, list, s);
-        else if (W == 2) launch_net<2, false>(p, o, f, flow_value, slots, list_count, list, s);
-        else launch_net<4, false>(p, o, f, flow_value, slots, list_count, list, s);
+        if (W == 1) launch_net<1, false>(p, o, f, flow_value, area, list, s);
+        else if (W == 2) launch_net<2, false>(p, o, f, flow_value, area, list, s);
+        else launch_net<4, false>(p, o, f, flow_value, area, list, s);
     }
     prof_mark(kKKv, true, s);
     return hipGetLastError();

@@ -120,14 +120,23 @@ constexpr int kArgSlots = 1024;
 __host__ __device__ inline unsigned long long argmax_key(int32_t value, int32_t n) {
     return ((unsigned long long)((uint32_t)value ^ 0x80000000u) << 32) | (unsigned long long)(0xFFFFFFFFu - (uint32_t)n);
 }
-// Folds the best key of a wavefront's lanes into slot blockIdx mod kArgSlots of arg with a 64-bit
+// Folds the best key of a wavefront's lanes into slot blockIdx mod kSlots of arg with a 64-bit
 // atomic max; every lane of the wavefront calls it (key 0: no candidate).
+template <int kSlots>
 __device__ __forceinline__ void fold_argmax(unsigned long long key, unsigned long long* arg) {
     for (int off = 32; off > 0; off >>= 1) {
         const unsigned long long o = __shfl_xor(key, off, 64);
         key = o > key ? o : key;
     }
-    if ((threadIdx.x & 63) == 0 && key != 0) atomicMax(&arg[blockIdx.x % kArgSlots], key);
+    if ((threadIdx.x & 63) == 0 && key != 0) atomicMax(&arg[blockIdx.x % kSlots], key);
+}
+// The argmax's area on the path of launch_score_net and launch_finish, in 64-bit words: kNetSlots slots,
+// then a line of 256 bytes with the count of listed candidates and the last ticket, then a line for each
+// of kNetTickets tickets (one atomic line for all of them serialised the workgroups).
+constexpr int kNetSlots = 512, kNetTickets = 16, kNetLine = 32;
+constexpr int kNetArea = kNetSlots + kNetLine * (1 + kNetTickets);
+__host__ __device__ inline int32_t* net_list_count(unsigned long long* area) {
+    return reinterpret_cast<int32_t*>(area + kNetSlots);
 }
 hipError_t launch_best_final(const unsigned long long* slots, int32_t* best, hipStream_t s);
 hipError_t launch_best_parts(const int32_t* flow_value, int32_t n, int32_t* best, int32_t* counter, uint64_t* part,
@@ -147,14 +156,13 @@ hipError_t launch_flownet_values(const Problem& p, const CostOut& o, const FlowN
                                  void* table, hipStream_t s);
 // hx_score_batch, replica networks of up to 32 group slots (score_net_fits): one kernel writes the
 // node and KV rows and every flow value that a closed form gives, and lists the other candidates
-// (*list_count, zero at launch); launch_finish solves those and reduces the argmax slots (zero at
-// launch) into best.  ticket: a zeroed word.
+// (list); launch_finish solves those and reduces the argmax slots into best.  area: kNetArea words, zero
+// at launch.
 bool score_net_fits(const Problem& p);
 hipError_t launch_score_net(const Problem& p, const CostOut& o, const FlowNet& f, int32_t* flow_value,
-                            unsigned long long* slots, int32_t* list_count, int32_t* list, hipStream_t s);
+                            unsigned long long* area, int32_t* list, hipStream_t s);
 hipError_t launch_finish(const Problem& p, const FlowNet& f, int32_t* flow_value, int32_t round_budget,
-                         unsigned long long* slots, const int32_t* list_count, const int32_t* list, int32_t* ticket,
-                         int32_t* best, hipStream_t s);
+                         unsigned long long* area, const int32_t* list, int32_t* best, hipStream_t s);
 bool maxflow_workgroup_plan(int32_t max_p, int32_t max_d, int32_t max_pd);
 hipError_t launch_maxflow_listed(const FlowNet& f, int32_t* flow_value, int32_t round_budget, const int32_t* list,
                                  const int32_t* count, hipStream_t s);

@@ -569,8 +569,8 @@ __global__ void __launch_bounds__(64) dom_kernel(FlowNet f, int32_t* flow_value)
 // The work of one tile (64/SEG candidates of a packed plan, or one candidate of a workgroup
 // plan); every lane of the workgroup calls it with the same tile.
 // kArg: fold the best of each wavefront's candidates (lane 0 of a segment holds its candidate's
-// key, argmax_key) into arg.  list: the tile's candidates are the tile-th kPer of the listed ones.
-template <int SEG, bool kStats, bool kArg = false>
+// key, argmax_key) into the kArg slots of arg.  list: the tile's candidates are the tile-th kPer of the listed ones.
+template <int SEG, bool kStats, int kArg = 0>
 __device__ __forceinline__ void maxflow_tile(const FlowNet& f, int32_t* flow_value, int32_t* kv_flow, uint8_t* cut,
                                              int32_t round_budget, unsigned long long* stats, int tile,
                                              unsigned long long* arg = nullptr, const int32_t* list = nullptr,
@@ -593,7 +593,7 @@ __device__ __forceinline__ void maxflow_tile(const FlowNet& f, int32_t* flow_val
         const int32_t pre = flow_value[n];
         if (pre >= 0) {
             if (kStats && l == 0) atomicAdd(&stats[HX_MF_PREPASS], 1ull);
-            if (kArg) fold_argmax(l == 0 ? argmax_key(pre, n) : 0ull, arg);
+            if constexpr (kArg > 0) fold_argmax<kArg>(l == 0 ? argmax_key(pre, n) : 0ull, arg);
             return;
         }
     }
@@ -1019,7 +1019,7 @@ __device__ __forceinline__ void maxflow_tile(const FlowNet& f, int32_t* flow_val
     __syncthreads();
     const int32_t value = cut_value >= 0 ? cut_value : (L.misc[1] ? HX_ENOCONV : L.misc[0]);
     if (valid && l == 0) flow_value[n] = value;
-    if (kArg) fold_argmax(l == 0 && in_range ? argmax_key(valid ? value : HX_EINVAL, n) : 0ull, arg);
+    if constexpr (kArg > 0) fold_argmax<kArg>(l == 0 && in_range ? argmax_key(valid ? value : HX_EINVAL, n) : 0ull, arg);
     if (valid && kv_flow)
         for (int e = l; e < P * D; e += SEG) {
             const int i = e / D, d = e - i * D;
@@ -1110,7 +1110,7 @@ __global__ void __launch_bounds__(SEG < 64 ? kPackedLanes : SEG, SEG <= 64 ? 8 :
     const int tiles = (f.N + kPer - 1) / kPer;
     const int chunk = (tiles + 7) / 8;
     const int tile = (int)(blockIdx.x & 7) * chunk + (int)(blockIdx.x >> 3);
-    maxflow_tile<SEG, kStats, kArg>(f, flow_value, kv_flow, cut, round_budget, stats, tile, arg);
+    maxflow_tile<SEG, kStats, kArg ? kArgSlots : 0>(f, flow_value, kv_flow, cut, round_budget, stats, tile, arg);
 }
 
 // Value only, workgroup plans: the candidates listed (list[0 .. *count), written by the kernel that
@@ -1128,24 +1128,62 @@ __global__ void __launch_bounds__(SEG) maxflow_list_kernel(FlowNet f, int32_t* f
 // The last kernel of hx_score_batch on replica networks: solves the candidates that net_kernel
 // listed (usually none), folding their values into the argmax slots, and reduces the slots.  With
 // nothing listed the first workgroup reduces them at once; otherwise the last workgroup to finish
-// (a ticket) does.
+// (tickets) does.
+//
+// The tiles of the list are dealt as maxflow_kernel's are, a contiguous eighth to the workgroups of each
+// XCD, and only the workgroups that have one take a ticket: workgroup y of XCD x ticket 2 x + (y mod 2), and
+// the last of each of these the last ticket.  The last workgroup reads nothing of the others' but what they
+// wrote with device-scope atomics, so each waits until its own are done and needs no release fence, which
+// would write back its XCD's L2.  The loop hides the network's dimensions from the compiler, which would
+// otherwise keep what it derives from them in registers across tiles (28 to 42 spilled).
+// What bounds it: the latency of a tile's dependent loads and LDS accesses, so up to 24 wavefronts a CU
+// (kFinishGrid; LDS 4 to 7 KB each), which cost a call with nothing listed no measurable time.
+// hx_score_batch with separate node, KV and max-flow kernels / with this kernel on 1,024 workgroups that
+// all took one ticket behind fences / now, 65,536 candidates: 5 networks listed of 4,096 (32 GPUs) 89 / 108 /
+// 73 us, 65,536 listed of 8 slots 182 / 261 / 183, 23,928 of 16 slots 119 / 171 / 98, 30,483 of 32 slots
+// 181 / 367 / 172, 64,102 of 16 slots that take push-relabel 657 / 1,408 / 727.
+constexpr int kFinishGrid = 6144;
+constexpr int kFinishParts = kNetTickets / 8;  // tickets of an XCD
+
+// Workgroups of XCD x that have a tile (rows: workgroups of an XCD).
+__device__ __forceinline__ int finish_workers(int x, int tiles, int chunk, int rows) {
+    const int left = tiles - x * chunk, t = left < chunk ? left : chunk;
+    return t < 0 ? 0 : (t < rows ? t : rows);
+}
+
 template <int SEG>
-__global__ void __launch_bounds__(kPackedLanes, 8)
-    finish_kernel(FlowNet f, int32_t* flow_value, int32_t round_budget, const int32_t* list, const int32_t* count,
-                  unsigned long long* slots, int32_t* ticket, int32_t* best) {
+__global__ void __launch_bounds__(kPackedLanes, 6)
+    finish_kernel(FlowNet f, int32_t* flow_value, int32_t round_budget, const int32_t* list, unsigned long long* area,
+                  int32_t* best) {
     static_assert(SEG <= 64, "packed plans");
     constexpr int kPer = kPackedLanes / SEG;
-    const int c = *count;
+    const int c = *net_list_count(area);
     if (c > 0) {
         __shared__ int32_t last;
-        for (int t = blockIdx.x; t * kPer < c; t += gridDim.x) {
-            maxflow_tile<SEG, false, true>(f, flow_value, nullptr, nullptr, round_budget, nullptr, t, slots, list, c);
+        const int tiles = (c + kPer - 1) / kPer, chunk = (tiles + 7) / 8, rows = (int)(gridDim.x >> 3);
+        const int x = (int)(blockIdx.x & 7), y = (int)(blockIdx.x >> 3);
+        const int mine = finish_workers(x, tiles, chunk, rows);
+        if (y >= mine) return;  // uniform
+        for (int i = y; i < chunk && x * chunk + i < tiles; i += rows) {
+            FlowNet g = f;
+            asm volatile("" : "+s"(g.N), "+s"(g.max_p), "+s"(g.max_d), "+s"(g.max_pd));
+            maxflow_tile<SEG, false, kNetSlots>(g, flow_value, nullptr, nullptr, round_budget, nullptr, x * chunk + i,
+                                                area, list, c);
             __syncthreads();  // the next candidates reuse the LDS
         }
         if (threadIdx.x == 0) {
-            __threadfence();
-            last = atomicAdd(ticket, 1) == (int32_t)gridDim.x - 1;
-            __threadfence();
+            int32_t* ticket = net_list_count(area) + 1;
+            const int q = y % kFinishParts, of = (mine - q + kFinishParts - 1) / kFinishParts;
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this wavefront's atomics are done
+            last = 0;
+            if (atomicAdd(net_list_count(area) + 2 * kNetLine * (1 + kFinishParts * x + q), 1) == of - 1) {
+                int parts = 0;  // tickets that some workgroup takes
+                for (int k = 0; k < 8; ++k) {
+                    const int w = finish_workers(k, tiles, chunk, rows);
+                    parts += w < kFinishParts ? w : kFinishParts;
+                }
+                last = atomicAdd(ticket, 1) == parts - 1;
+            }
         }
         __syncthreads();
         if (!last) return;  // uniform
@@ -1154,8 +1192,8 @@ __global__ void __launch_bounds__(kPackedLanes, 8)
     }
     unsigned long long key = 0;
 #pragma unroll
-    for (int i = 0; i < kArgSlots / kPackedLanes; ++i) {
-        const unsigned long long v = __hip_atomic_load(&slots[i * kPackedLanes + threadIdx.x], __ATOMIC_RELAXED,
+    for (int i = 0; i < kNetSlots / kPackedLanes; ++i) {
+        const unsigned long long v = __hip_atomic_load(&area[i * kPackedLanes + threadIdx.x], __ATOMIC_RELAXED,
                                                        __HIP_MEMORY_SCOPE_AGENT);
         key = v > key ? v : key;
     }
@@ -1251,8 +1289,7 @@ hipError_t launch_maxflow_listed(const FlowNet& f, int32_t* flow_value, int32_t 
 }
 
 hipError_t launch_finish(const Problem& p, const FlowNet& f, int32_t* flow_value, int32_t round_budget,
-                         unsigned long long* slots, const int32_t* list_count, const int32_t* list, int32_t* ticket,
-                         int32_t* best, hipStream_t s) {
+                         unsigned long long* area, const int32_t* list, int32_t* best, hipStream_t s) {
     // the networks have at most Kmax nodes in all, whatever room the caller's arrays have
     FlowNet t = f;
     t.max_p = t.max_d = p.Kmax;
@@ -1262,17 +1299,17 @@ hipError_t launch_finish(const Problem& p, const FlowNet& f, int32_t* flow_value
     const int per = kPackedLanes / seg;
     const size_t lds = per * mf_words(t.max_p, t.max_d, t.max_pd) * sizeof(int32_t);
     const int tiles = (f.N + per - 1) / per;
-    const dim3 grid(tiles < 1024 ? tiles : 1024);
+    const dim3 grid(8 * (((tiles < kFinishGrid ? tiles : kFinishGrid) + 7) / 8));
     prof_mark(kKMaxflow, false, s);
     if (seg == 8)
-        hipLaunchKernelGGL(finish_kernel<8>, grid, dim3(kPackedLanes), lds, s, t, flow_value, round_budget, list,
-                           list_count, slots, ticket, best);
+        hipLaunchKernelGGL(finish_kernel<8>, grid, dim3(kPackedLanes), lds, s, t, flow_value, round_budget, list, area,
+                           best);
     else if (seg == 16)
-        hipLaunchKernelGGL(finish_kernel<16>, grid, dim3(kPackedLanes), lds, s, t, flow_value, round_budget, list,
-                           list_count, slots, ticket, best);
+        hipLaunchKernelGGL(finish_kernel<16>, grid, dim3(kPackedLanes), lds, s, t, flow_value, round_budget, list, area,
+                           best);
     else
-        hipLaunchKernelGGL(finish_kernel<32>, grid, dim3(kPackedLanes), lds, s, t, flow_value, round_budget, list,
-                           list_count, slots, ticket, best);
+        hipLaunchKernelGGL(finish_kernel<32>, grid, dim3(kPackedLanes), lds, s, t, flow_value, round_budget, list, area,
+                           best);
     prof_mark(kKMaxflow, true, s);
     return hipGetLastError();
 }

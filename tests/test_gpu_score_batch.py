@@ -281,6 +281,43 @@ def test_score_batch_replica_networks(torch, gpus, groups, n, slow, room):
     assert np.array_equal(out[1]["flow_value"][idx], want["flow_value"])
 
 
+@pytest.mark.parametrize("groups,n,every", [(8, 3, 1), (8, 70000, 1), (16, 65, 1), (16, 30000, 1), (32, 3, 1), (32, 20000, 1),
+                                            (16, 4096, 1500), (16, 4096, 300), (8, 4096, 50), (32, 4096, 9)])
+def test_score_batch_listed_networks(torch, groups, n, every):
+    """The last kernel of the fused call from one listed network up: every candidate with groups of four
+    GPUs, which all have a strategy, over links too slow for them (so no closed form settles it), or every
+    n-th one and the others without a decode group; fewer and more listed than its workgroups take at
+    once.  Flow values equal the four calls', best is the first maximum, call after call on a dirty
+    workspace."""
+    gpus = 4 * groups
+    rng = np.random.default_rng([2502, groups, n, every])
+    inter = np.triu(rng.uniform(3.0, 25.0, (groups, groups)), 1) * 1e9
+    tab = np.array([I.GPU_TYPES[c] for c in "AB"])
+    cl = I.cluster_from_nodes(np.repeat(np.arange(groups) % 2, 4).astype(np.int32), tab, inter + inter.T)
+    cl = dataclasses.replace(cl, beta=np.ascontiguousarray(cl.beta / 1000))
+    assign = np.argsort(rng.random((n, gpus)), 1).argsort(1).T // 4
+    role = np.repeat((np.arange(groups) % 2)[:, None], n, 1)
+    role[:, np.arange(n) % every != 0] = I.PREFILL
+    prob = I.Problem(cl, dict(I.OPT_30B), 1024.0, 256.0, I._mask((1, 2, 4, 8)), I._mask(range(1, 9)), 0, groups,
+                     np.ascontiguousarray(assign, np.uint8), np.ascontiguousarray(role, np.uint8))
+    dp = hx.DeviceProblem.upload(prob)
+    ws = hx.Workspace.for_problem(dp, flows=False)
+    hx.score(dp, ws)
+    st = hx.maxflow_stats(ws.net, torch.empty_like(ws.flow_value))
+    want = ws.flow_value.cpu().numpy()
+    say(f"hx_score_batch: {groups} slots, N={n}, every {every}: {st}")
+    listed = st["min_cut"] + st["push_relabel"]
+    assert listed > 0.5 * n / every and listed <= -(-n // every)
+    for fill in (0xA5, 0xFF):
+        ws.cost.workspace.fill_(fill)
+        ws.flow_value.fill_(-7)
+        hx.score_batch(dp, ws)
+        torch.cuda.synchronize()
+        got = ws.flow_value.cpu().numpy()
+        assert np.array_equal(got, want)
+        assert ws.best.tolist() == [int(np.argmax(want)), int(want.max())]
+
+
 def test_score_batch_concurrent_streams(torch):
     """Independent calls in flight on three streams (each with its own workspace and outputs, the
     inputs shared): every stream's flow values and best equal a single-stream call's, call after
