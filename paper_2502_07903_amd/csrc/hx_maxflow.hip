@@ -158,26 +158,35 @@ __device__ __forceinline__ void mf_wave_sync() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// The bit words of the flow in L, by every lane l of the workgroup (followed by a barrier).
+// The bit words of the flow in L (flows: it is not all zero), by every lane l of the workgroup (followed by
+// a barrier).  Eight LDS reads at a time, the last repeated past the end: one after another they made the
+// flows and cuts of 1,024 networks of 100 x 27 nodes without flow 38 us instead of 35.
 template <int SEG>
-__device__ __forceinline__ void residual_bits(MfBits<SEG>& S, const MfLayout& L, int l, int P, int D, int Ds) {
+__device__ __forceinline__ void residual_bits(MfBits<SEG>& S, const MfLayout& L, int l, int P, int D, int Ds, bool flows) {
     constexpr int kM = MfBits<SEG>::kM;
-    if (l < P)
+    auto word = [](int n, auto bit) {  // bits 0 .. n - 1
+        uint64_t m = 0;
+        for (int x0 = 0; x0 < n; x0 += 8)
 #pragma unroll
-        for (int w = 0; w < kM; ++w) {
-            uint64_t m = 0;
-            const int hi = D - 64 * w < 64 ? D - 64 * w : 64;
-            for (int x = 0; x < hi; ++x) m |= (uint64_t)(L.cap[l * Ds + 64 * w + x] - L.fl[l * Ds + 64 * w + x] > 0) << x;
-            S.room[l][w] = m;
-        }
-    if (l < D)
+            for (int k = 0; k < 8; ++k) {
+                const int x = x0 + k < n ? x0 + k : n - 1;
+                m |= (uint64_t)bit(x) << x;
+            }
+        return m;
+    };
 #pragma unroll
-        for (int w = 0; w < kM; ++w) {
-            uint64_t m = 0;
-            const int hi = P - 64 * w < 64 ? P - 64 * w : 64;
-            for (int x = 0; x < hi; ++x) m |= (uint64_t)(L.fl[(64 * w + x) * Ds + l] > 0) << x;
-            S.used[l][w] = m;
+    for (int w = 0; w < kM; ++w) {
+        if (l < P) {
+            const int32_t *c = L.cap + l * Ds + 64 * w, *fl = L.fl + l * Ds + 64 * w;
+            const int n = D - 64 * w < 64 ? D - 64 * w : 64;
+            S.room[l][w] = flows ? word(n, [&](int x) { return c[x] - fl[x] > 0; }) : word(n, [&](int x) { return c[x] > 0; });
         }
+        if (l < D) {
+            const int32_t* fl = L.fl + 64 * w * Ds + l;
+            const int n = P - 64 * w < 64 ? P - 64 * w : 64;
+            S.used[l][w] = flows ? word(n, [&](int x) { return fl[x * Ds] > 0; }) : 0;
+        }
+    }
 }
 
 // Decode node j returns up to e of its excess over the arcs of word w in m; returns the rest.
@@ -686,9 +695,12 @@ __device__ __forceinline__ void maxflow_tile(const FlowNet& f, int32_t* flow_val
             }
         }
     } else if (has_flow || kv_flow != nullptr || cut != nullptr) {
-        // sixteen rows' loads in flight per lane (rows past the last read it again and are dropped); the
-        // dominance test on the way
-        constexpr int kBatch = 16;
+        // four rows' loads in flight per lane (rows past the last read it again and are dropped); the
+        // dominance test on the way.  (More of them pull the lines that neighbouring candidates share out of
+        // the L2: 4,096 networks of 64 x 64 nodes with their flows, 174 us without flow and 192 dominant with
+        // four, 190 and 202 with eight, 206 and 205 with sixteen, 172 and 231 before the test was joined to the
+        // loads.)
+        constexpr int kBatch = 4;
         const int E = P * D;
         for (int e0 = l; e0 < E; e0 += kBatch * SEG) {
             int32_t v[kBatch];
@@ -915,7 +927,7 @@ __device__ __forceinline__ void maxflow_tile(const FlowNet& f, int32_t* flow_val
     if constexpr (SEG > 64) {
         // (more than SEG nodes a side, which only arrays wider than 256 rows hold, stay with the loop below)
         if (path == HX_MF_PUSH_RELABEL && P <= SEG && D <= SEG) {  // uniform: one candidate per workgroup
-            residual_bits<SEG>(B, L, l, P, D, Ds);
+            residual_bits<SEG>(B, L, l, P, D, Ds, false);
             __syncthreads();
             if (threadIdx.x < 64)
                 left = push_relabel_bits<SEG, kStats>(B, L, l, P, D, Ds, round_budget,
@@ -1034,7 +1046,7 @@ __device__ __forceinline__ void maxflow_tile(const FlowNet& f, int32_t* flow_val
     if constexpr (SEG > 64) {
         if (P <= SEG && D <= SEG) {
             if (path != HX_MF_PUSH_RELABEL) {  // uniform
-                residual_bits<SEG>(B, L, l, P, D, Ds);
+                residual_bits<SEG>(B, L, l, P, D, Ds, path != HX_MF_NO_FLOW);
                 __syncthreads();
             }
             if (threadIdx.x < 64) cut_bits<SEG>(B, L, f, cut, n, l, P, D);
