@@ -136,15 +136,26 @@ __global__ void __launch_bounds__((kB + 3) / 4 * 64) spectral_kernel(int G, cons
                     s = s + row[e0 + 2 * i + 1] * c[i].y;
                 }
             }
-        } else if (d < G) {
-            constexpr int kC = 8;
+        } else {
+            // kC weights in flight while the chunk before is summed; lanes past G read the last column, rows
+            // past G the last row, where x is 0 as above.  1,000 iterations at 129, 160, 200, 255 GPUs: 7.8, 9.4,
+            // 11.7, 15.4 ms with one lane forming the sums, 10.7, 12.5, 16.6, 20.7 with eight weights loaded, then
+            // summed, 6.2, 6.7, 8.2, 9.6 now (32 or 64 weights: 10.9 and 12.9 at 255).
+            constexpr int kC = 16;
+            const int dc = d < G ? d : G - 1;
+            int64_t next[kC];
+            auto load = [&](int e0) {
+#pragma unroll
+                for (int i = 0; i < kC; ++i) next[i] = w[(int64_t)(e0 + i < G ? e0 + i : G - 1) * G + dc];
+            };
+            load(0);
             for (int e0 = 0; e0 < G; e0 += kC) {
-                int64_t v[kC];  // rows past G read row G - 1 and are dropped
+                int64_t v[kC];
 #pragma unroll
-                for (int i = 0; i < kC; ++i) v[i] = w[(int64_t)(e0 + i < G ? e0 + i : G - 1) * G + d];
+                for (int i = 0; i < kC; ++i) v[i] = next[i];
+                if (e0 + kC < G) load(e0 + kC);
 #pragma unroll
-                for (int i = 0; i < kC; ++i)
-                    if (e0 + i < G) s = s + (double)v[i] * x[e0 + i];
+                for (int i = 0; i < kC; ++i) s = s + (double)v[i] * x[e0 + i];
             }
         }
         const double yv = (cap - dg) * xd + s;

@@ -154,7 +154,8 @@ def test_partition_workspace_is_the_weight_table(torch, gpus, links):
     (33, 32, 40, False, 1.0), (49, 9, 21, True, 1.0), (64, 32, 30, True, 1.0), (65, 8, 12, False, 1.0), (81, 32, 6, False, 1.0),
     (104, 32, 5, True, 1.0), (105, 32, 5, False, 1.0), (113, 20, 4, False, 1.0), (128, 32, 4, True, 1.0),
     (129, 32, 3, False, 1.0), (255, 32, 2, False, 1.0), (20, 8, 40, False, 2e4),
-    (20, 8, 1100, False, 2e4), (6, 3, 16700, False, 2e4), (64, 32, 20, True, 2e4), (130, 8, 3, False, 2e4)])
+    (20, 8, 1100, False, 2e4), (6, 3, 16700, False, 2e4), (64, 32, 20, True, 2e4), (130, 8, 3, False, 2e4),
+    (144, 8, 3, False, 1.0), (145, 8, 3, True, 1.0)])
 def test_partition_sizes(torch, gpus, groups, n, ties, links):
     """The spectral order and the candidates around every size switch (lane sets of 32 to 256, rows of
     16-GPU chunks, weights staged or read), with ties (every link of a kind alike, so that many
