@@ -162,7 +162,8 @@ __device__ __forceinline__ void mf_wave_sync() {
 // a barrier).  Eight LDS reads at a time, the last repeated past the end: one after another they made the
 // flows and cuts of 1,024 networks of 100 x 27 nodes without flow 38 us instead of 35.
 template <int SEG>
-__device__ __forceinline__ void residual_bits(MfBits<SEG>& S, const MfLayout& L, int l, int P, int D, int Ds, bool flows) {
+__device__ __forceinline__ void residual_bits(MfBits<SEG>& S, const MfLayout& L, int l, int P, int D, int Ds,
+                                              bool flows) {
     constexpr int kM = MfBits<SEG>::kM;
     auto word = [](int n, auto bit) {  // bits 0 .. n - 1
         uint64_t m = 0;
@@ -179,7 +180,8 @@ __device__ __forceinline__ void residual_bits(MfBits<SEG>& S, const MfLayout& L,
         if (l < P) {
             const int32_t *c = L.cap + l * Ds + 64 * w, *fl = L.fl + l * Ds + 64 * w;
             const int n = D - 64 * w < 64 ? D - 64 * w : 64;
-            S.room[l][w] = flows ? word(n, [&](int x) { return c[x] - fl[x] > 0; }) : word(n, [&](int x) { return c[x] > 0; });
+            S.room[l][w] = flows ? word(n, [&](int x) { return c[x] - fl[x] > 0; })
+                                 : word(n, [&](int x) { return c[x] > 0; });
         }
         if (l < D) {
             const int32_t* fl = L.fl + 64 * w * Ds + l;
@@ -925,8 +927,9 @@ __device__ __forceinline__ void maxflow_tile(const FlowNet& f, int32_t* flow_val
     if (kStats && valid && l == 0) atomicAdd(&stats[path], 1ull);
     __shared__ MfBits<(SEG > 64 ? SEG : 64)> B;  // (workgroup plans)
     if constexpr (SEG > 64) {
-        // (more than SEG nodes a side, which only arrays wider than 256 rows hold, stay with the loop below)
-        if (path == HX_MF_PUSH_RELABEL && P <= SEG && D <= SEG) {  // uniform: one candidate per workgroup
+        // (more than SEG nodes a side, which only arrays wider than 256 rows hold, stay with the loop below; the
+        // 128-lane plan's arrays hold at most 128 a side, so it has neither the loop nor the heights it needs)
+        if (path == HX_MF_PUSH_RELABEL && (SEG == 128 || (P <= SEG && D <= SEG))) {  // uniform: one candidate a workgroup
             residual_bits<SEG>(B, L, l, P, D, Ds, false);
             __syncthreads();
             if (threadIdx.x < 64)
@@ -936,7 +939,7 @@ __device__ __forceinline__ void maxflow_tile(const FlowNet& f, int32_t* flow_val
             active = false;
         }
     }
-    for (int round = 0; __syncthreads_or(active) && round < round_budget; ++round) {
+    for (int round = 0; SEG != 128 && __syncthreads_or(active) && round < round_budget; ++round) {
         if (kStats && threadIdx.x == 0) {
             atomicAdd(&stats[HX_MF_ROUNDS], 1ull);
             if (round % kGlobalRelabelEvery == 0) atomicAdd(&stats[HX_MF_GLOBAL_RELABELS], 1ull);
@@ -1044,7 +1047,7 @@ __device__ __forceinline__ void maxflow_tile(const FlowNet& f, int32_t* flow_val
     if (!cut) return;  // uniform across the workgroup
 
     if constexpr (SEG > 64) {
-        if (P <= SEG && D <= SEG) {
+        if (SEG == 128 || (P <= SEG && D <= SEG)) {
             if (path != HX_MF_PUSH_RELABEL) {  // uniform
                 residual_bits<SEG>(B, L, l, P, D, Ds, path != HX_MF_NO_FLOW);
                 __syncthreads();

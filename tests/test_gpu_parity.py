@@ -424,12 +424,15 @@ def test_maxflow_round_budget_reports_noconv(torch, monkeypatch):
 
 
 @pytest.mark.parametrize("P,D,rows", [(40, 3, 65), (64, 64, 65), (65, 60, 65), (128, 30, 128), (30, 128, 128), (129, 28, 129),
-                                      (25, 200, 200), (255, 20, 255), (220, 32, 220), (17, 9, 300)])
+                                      (25, 200, 200), (255, 20, 255), (220, 32, 220), (17, 9, 300), (256, 16, 300),
+                                      (260, 8, 300), (300, 8, 300), (8, 300, 300), (88, 88, 88)])
 def test_maxflow_workgroup_plans(torch, monkeypatch, P, D, rows):
     """Binding networks on the workgroup plans (arrays of `rows` rows a side: 65 to 128 take 128 lanes and two
-    bit words a node, up to 256 four; 300 rows are past the bit words): values equal the oracle's with and
-    without flows, the flows are valid maximum flows and the cut is the canonical one; with a budget of
-    one round some networks report HX_ENOCONV and the others their value."""
+    bit words a node, more rows four; networks of more than 256 nodes a side, in 300 rows here, run on a lane
+    per node as the packed plans do, 17 x 9 to 256 x 16 nodes in 300 rows on the bit words; 88 x 88 nodes take
+    nearly all the LDS of a plan): values equal the oracle's with and without flows, the flows are valid
+    maximum flows and the cut is the canonical one; with a budget of one round some networks report
+    HX_ENOCONV and the others their value."""
     rng = np.random.default_rng([77, P, D])
     N, mpd = 40, P * D
     n_p = np.maximum(1, P - rng.integers(0, 3, N)).astype(np.int32)
