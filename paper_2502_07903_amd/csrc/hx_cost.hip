@@ -624,8 +624,9 @@ __global__ void __launch_bounds__(256) decode_kernel(Problem p, CostOut o, CostW
             }
             if (costed && hit < 0) atomicAdd(&lhist[bucket_of(p.G, size, rl[x])], 1);
             // Every slot is written, whole cache lines at a time (eval later writes the costed ones over):
-            // a partly written line costs a read.  The outputs that no later kernel of a call reads go
-            // past the caches.  64 GPUs x 262,144 candidates: 63.9 -> 59.8 us.
+            // a partly written line costs a read.  The batch limits and latencies, which no later kernel of a
+            // call reads, go past the caches (the KV walks read the strategies, the node kernels the
+            // capacities).  64 GPUs x 262,144 candidates: 63.9 -> 59.8 us.
             uint8_t v_tp = 0, v_pp = 0;
             int32_t v_bmax = 0, v_cap = 0;
             double v_lat = 0.0;
@@ -637,7 +638,7 @@ __global__ void __launch_bounds__(256) decode_kernel(Problem p, CostOut o, CostW
                 v_lat = ref.out.lat[hit];
             }
             o.tp[o_] = v_tp;
-            __builtin_nontemporal_store(v_pp, &o.pp[o_]);
+            o.pp[o_] = v_pp;
             __builtin_nontemporal_store(v_bmax, &o.bmax[o_]);
             o.cap[o_] = v_cap;
             __builtin_nontemporal_store(v_lat, &o.lat[o_]);
