@@ -681,7 +681,7 @@ __device__ __forceinline__ uint32_t set_nib(uint32_t v, int i, int x) {
 // 1.32 ms at 32 GPUs x 16,384 candidates; whole calls with 64 and 8: 3.64 and 2.44 ms at x 65,536, 5.59
 // and 1.95 ms at 64 GPUs x 4,096.
 constexpr int kOrderLanes = 8;
-constexpr int64_t kOrderGrid = 1 << 22;  // workgroups of a launch in x, at most
+constexpr int64_t kOrderGrid = 1 << 22;  // workgroups of a launch, at most
 constexpr int kOrderThreads = 256;  // kv_order_kernel: wave 0 holds the lanes, all four waves search
 constexpr int kOrderLevels = 4;     // search levels below a queued prefix, at most
 constexpr int kOrderQueue = 2 * kOrderThreads;  // prefixes handed out per edge, at least (when nx allows)
@@ -821,19 +821,20 @@ __device__ __forceinline__ void order_search(OrderShared& S, int nx, int ny, int
 // bound below every order pair (pairs_bound, the largest over the threads).  The minimum is the
 // one the enumeration of every order pair finds.  Per-replica granularity.
 //
-// The lanes cover the first `rows` KV rows of every candidate, kOrderLanes a workgroup, over a grid of
-// kOrderGrid workgroups a row of y: HIP takes less than 2^32 threads in a dimension, which a grid of one
-// dimension would reach at 2^27 (edge, candidate) cells.
+// The lanes cover the first max_pd KV rows of every candidate from cell `first` on, kOrderLanes a
+// workgroup, in launches of up to kOrderGrid workgroups: HIP takes less than 2^32 threads in a dimension,
+// which one launch would reach at 2^27 (edge, candidate) cells.  (A grid of two dimensions measured 1%
+// slower at 32 GPUs x 65,536, a loop in the kernel 16% at 64 x 32,768.)
 template <int W>
-__global__ void __launch_bounds__(kOrderThreads) kv_order_kernel(Problem p, CostOut o, FlowNet f, int rows) {
+__global__ void __launch_bounds__(kOrderThreads) kv_order_kernel(Problem p, CostOut o, FlowNet f, int64_t first) {
     extern __shared__ __attribute__((aligned(16))) uint8_t sm[];
     OrderShared& S = *reinterpret_cast<OrderShared*>(sm);
     uint8_t* mem = sm + kOrderLds;
     const int tid = threadIdx.x;
     const int stride = kOrderLanes;
-    const int64_t gid = ((int64_t)blockIdx.y * kOrderGrid + blockIdx.x) * kOrderLanes + tid;
+    const int64_t gid = first + (int64_t)blockIdx.x * kOrderLanes + tid;
     const int64_t N = p.N;
-    bool live = tid < kOrderLanes && gid < (int64_t)rows * N;
+    bool live = tid < kOrderLanes && gid < (int64_t)f.max_pd * N;
     const int e = live ? (int)(gid / N) : 0;
     const int n = live ? (int)(gid - (int64_t)e * N) : 0;
     const int np = live ? f.n_p[n] : 0, nd = live ? f.n_d[n] : 0;
@@ -1615,9 +1616,11 @@ hipError_t launch_w(const Problem& p, const CostOut& o, const FlowNet& f, hipStr
         if (e != hipSuccess) return e;
     } else if (p.variant & HX_VARIANT_KV_ORDER) {
         const int64_t wgs = ((int64_t)rows * p.N + kOrderLanes - 1) / kOrderLanes;
-        const dim3 grid((unsigned)(wgs < kOrderGrid ? wgs : kOrderGrid), (unsigned)((wgs + kOrderGrid - 1) / kOrderGrid));
-        hipLaunchKernelGGL(kv_order_kernel<W>, grid, dim3(kOrderThreads), kOrderLds + 2 * (size_t)p.G * kOrderLanes, s, p,
-                           o, f, rows);
+        FlowNet g = f;
+        g.max_pd = rows;
+        for (int64_t at = 0; at < wgs; at += kOrderGrid)
+            hipLaunchKernelGGL(kv_order_kernel<W>, dim3((unsigned)(wgs - at < kOrderGrid ? wgs - at : kOrderGrid)),
+                               dim3(kOrderThreads), kOrderLds + 2 * (size_t)p.G * kOrderLanes, s, p, o, g, at * kOrderLanes);
     } else if (p.variant & HX_VARIANT_ASYM) {
         hipLaunchKernelGGL((kv_kernel<W, true, false>), grid_kv, dim3(kKvBlock), lds + sizeof(double) * p.G, s, p,
                            o, f);
