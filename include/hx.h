@@ -26,7 +26,7 @@
  * and the graph-partition phase of Sec. 3.2 that generates candidates in the first place:
  *
  *   hx_spectral_order        the Fiedler order of the device graph  (one workgroup)
- *   hx_partition_candidates  partition, swaps, role split per draw  (one workgroup per candidate)
+ *   hx_partition_candidates  partition, swaps, role split per draw  (a wavefront or workgroup per candidate)
  *
  * Conventions
  *   - Every array pointer is a DEVICE pointer unless marked [host].  The caller owns every
@@ -312,13 +312,14 @@ int hx_best_candidate(const int32_t *flow_value, int32_t n_cand, int32_t *best, 
  * workgroups fold into; 256-byte aligned, contents ignored on entry), and the same results: every cost
  * output, the network's node counts (n_p, n_d), flow_value and best, bit for bit.  At
  * granularity 0, and beyond 128 GPUs or 128 group slots, every row of the network is written as
- * by hx_build_flownet (with up to 32 group slots one kernel writes the rows and settles the values
- * that have a closed form, and only the other networks are solved from their rows).  At
- * granularity 1 on clusters of up to 128 GPUs a KV edge's capacity depends only on its link,
- * so a network whose every KV edge can carry min(a_i, b_j) (the dominant-KV closed form: maximum flow min(sum a, sum b)) is settled from a table of link
- * capacities while its nodes are counted, and only the other networks get their node and KV rows
- * written and are solved by push-relabel; the rows of the settled networks are left as they
- * were. */
+ * by hx_build_flownet (with up to 32 group slots, and neither HX_VARIANT_ASYM nor
+ * HX_VARIANT_KV_ORDER, one kernel writes the rows and settles the values that have a closed form,
+ * and only the other networks are solved from their rows).  At granularity 1 on clusters of up to
+ * 128 GPUs a KV edge's capacity depends only on its link, so a network whose every KV edge can
+ * carry min(a_i, b_j) (the dominant-KV closed form: maximum flow min(sum a, sum b)) is settled from
+ * a table of link capacities while its nodes are counted, and only the other networks get their
+ * node and KV rows written and are solved by push-relabel; the rows of the settled networks are
+ * left as they were. */
 size_t hx_score_workspace_bytes(int32_t n_gpus, int32_t max_groups, int32_t n_cand);
 int hx_score_batch(const hx_cluster *cluster, hx_model model, hx_workload wl, hx_space space,
                    const hx_candidates *cand, const hx_cost_out *cost, const hx_flownet *net, int32_t *flow_value,
@@ -383,7 +384,8 @@ int hx_gather_candidates(int32_t n_gpus, const hx_candidates *src, const int32_t
  * by a cut of maximum weight, and the partition is projected back onto the GPUs.  Edge weights
  * are w_de = floor(((beta_de + beta_ed) * 0.5) / 1e6) clamped to [0, 2^47] (whole MB/s; the
  * bound keeps every cut of up to 255 GPUs below 2^62), node weights the memory limits in whole
- * bytes, so cuts, gains and their sums are exact 64-bit integer sums. */
+ * bytes, so cuts, gains and their sums are exact whole numbers of up to 64 bits (held as 32-bit
+ * integers and whole binary64 numbers where every value of the graph fits those exactly). */
 
 /* Device scratch both calls need (an [n_gpus][n_gpus] int64 weight table they fill first);
  * 0 for n_gpus outside [2, 255]. */
@@ -415,7 +417,8 @@ int hx_spectral_order(const hx_cluster *cluster, int32_t iters, void *workspace,
  *       the flip with the largest gain (lowest k on ties) is applied; side 0 = prefill;
  *   step (iii): assign[g][n] = the group of GPU g, role[k][n] = its side for k below the group
  *       count, HX_UNUSED beyond.
- *   order: the spectral order (hx_spectral_order).  One workgroup per candidate. */
+ *   order: the spectral order (hx_spectral_order).  A wavefront per candidate up to 64 GPUs, a workgroup
+ *   above, and for graphs past the exact 32-bit and binary64 ranges. */
 int hx_partition_candidates(const hx_cluster *cluster, hx_model model, hx_workload wl, int32_t max_groups,
                             void *workspace, size_t workspace_bytes, const int32_t *order, int32_t n_cand,
                             const uint64_t *rnd, uint8_t *assign, uint8_t *role, hipStream_t stream);
@@ -429,7 +432,11 @@ int hx_partition_candidates(const hx_cluster *cluster, hx_model model, hx_worklo
  * gives kernel k's name: setup, decode, scatter, eval (hx_cost_eval), nodes, kv
  * (hx_build_flownet), maxflow, best, classes (hx_edge_classes), moves (hx_guided_moves),
  * gather (hx_gather_candidates), spectral (hx_spectral_order), partition
- * (hx_partition_candidates), shared (candidate 0's groups under HX_HINT_SHARED_GROUPS). */
+ * (hx_partition_candidates), shared (candidate 0's groups under HX_HINT_SHARED_GROUPS).  The
+ * kernels that hx_score_batch joins have one name: on replica networks that one kernel builds and
+ * settles, kv holds the nodes, KV edges and settled values, maxflow the listed networks and the
+ * argmax, nodes and best nothing; on per-GPU networks kv is the table of links, nodes the nodes
+ * and settled values. */
 #define HX_KERNELS 14
 int hx_profile(int32_t enable);
 int hx_profile_read(double *ms, int32_t *launches, int32_t n);

@@ -1079,8 +1079,8 @@ __device__ __forceinline__ void lane_sync() {
 }
 
 // The replica networks of hx_score_batch in one kernel (up to 32 group slots, uniform split): a
-// workgroup per 64 candidates lists their nodes, walks their KV edges and settles their flow
-// values, where nodes_kernel, kv_kernel and the max-flow kernel would each read the network back.
+// workgroup per C = 16, 32 or 64 candidates lists their nodes, walks their KV edges and settles their
+// flow values, where nodes_kernel, kv_kernel and the max-flow kernel would each read the network back.
 //   nodes   256 / C lanes per candidate take the group slots; a slot's node index is the number of
 //           its side's slots below it, from bit masks met in LDS;
 //   rows    every KV row below n_p n_d is written 0, those lanes taking the rows in turn, then the
@@ -1345,9 +1345,9 @@ __global__ void __launch_bounds__(kNetBlock) net_kernel(Problem p, CostOut o, Fl
         }
     }
     if (part == 0 && df != 0) S.recip[ci] = (65536u + (uint32_t)__popc(df) - 1) / (uint32_t)__popc(df);
-    // KV rows: zeros, this lane every kParts-th row, past the caches (nothing in the call reads them, and
-    // 64 GPUs x 262,144 candidates write 92 MB of them: the call took 616 us with ordinary stores, 584
-    // with these, 17 us of it in the next call's first kernels)
+    // KV rows: zeros, this lane every kParts-th row, past the caches (only listed networks read theirs
+    // back, in finish_kernel, and 64 GPUs x 262,144 candidates write 92 MB of them: the call took 616 us with
+    // ordinary stores, 584 with these, 17 us of it in the next call's first kernels)
     const int pd = np * nd;
     {
         int32_t* row = f.kv_cap + (int64_t)part * N + n;

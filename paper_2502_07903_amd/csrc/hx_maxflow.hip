@@ -420,7 +420,7 @@ __device__ __forceinline__ void cut_bits(const MfBits<SEG>& S, const MfLayout& L
         pout[s] = fresh[s] = pin[s] && f.p_cap[o] - fs[s] > 0;
         din[s] = false;
     }
-    // the OR over the fresh nodes' words: word w in lane w
+    // the OR over the fresh nodes' words, in every lane
     auto offered = [&](const uint64_t (*words)[kM], uint64_t (&out)[kM]) {
 #pragma unroll
         for (int w = 0; w < kM; ++w) {
@@ -459,7 +459,8 @@ __device__ __forceinline__ void cut_bits(const MfBits<SEG>& S, const MfLayout& L
         const int64_t o = (int64_t)v * N + n;
         pin[s] |= pout[s] && fs[s] > 0;
         if (v < P) cut[o] = (uint8_t)((pin[s] ? 1 : 0) | (pout[s] ? 2 : 0));
-        if (v < D) cut[(int64_t)f.max_p * N + o] = (uint8_t)((din[s] ? 1 : 0) | (din[s] && f.d_cap[o] - L.ft[v] > 0 ? 2 : 0));
+        if (v < D)
+            cut[(int64_t)f.max_p * N + o] = (uint8_t)((din[s] ? 1 : 0) | (din[s] && f.d_cap[o] - L.ft[v] > 0 ? 2 : 0));
     }
 }
 

@@ -14,9 +14,10 @@
 //   partition_gain_kernel, partition_kernel  a candidate each: (i) the rotated spectral order cut into K
 //                     memory-balanced groups, then Kernighan-Lin passes: every pair of GPUs has its
 //                     swap's gain, kept up to date in registers (or, past the exact ranges of
-//                     binary64, formed anew from per-GPU group sums), a maximum over them picks the largest reduction (negative ones too; lowest pair on ties), the
-//                     swap is made tentatively and its two GPUs locked; the pass keeps its best
-//                     prefix and undoes the rest; (ii) groups coarsened into super nodes (LDS
+//                     binary64, formed anew from per-GPU group sums), a maximum over them picks the
+//                     largest reduction (negative ones too; lowest pair on ties), the swap is made
+//                     tentatively and its two GPUs locked; the pass keeps its best prefix and undoes
+//                     the rest; (ii) groups coarsened into super nodes (LDS
 //                     atomics) and split into prefill and decode by single flips that raise the
 //                     cut; (iii) the projection written as the candidate's assign and role columns.
 // Graph and integer work: no MFMA.
