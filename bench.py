@@ -51,40 +51,38 @@ FP64_VALU_PEAK_GOPS = 256 * 4 * 16 * 2.4
 # taken on (first 16 hex digits of the source file's SHA-256); otherwise traffic is null.
 COUNTER_SCALE = {"fetch": 2.0, "write": 1.0}
 KERNEL_TRAFFIC = {
-    # workload 3 (profiles/all_kernels_workload3.md); taken on the six-launch network path
-    # that the fused network kernel replaced: the hashes differ, so no traffic is reported from it
+    # workload 3, hx_score_batch (profiles/all_kernels_workload3.md): kv is the network kernel (nodes,
+    # KV edges and settled values), maxflow the last kernel (listed networks, argmax)
     3: {
-        "setup": {"source_sha256_16": "cfe308a8f566cbcf", "fetch_kib": 70.55, "write_kib": 57.43},
-        "decode": {"source_sha256_16": "cfe308a8f566cbcf", "fetch_kib": 1714, "write_kib": 2.884e+04},
-        "scatter": {"source_sha256_16": "cfe308a8f566cbcf", "fetch_kib": 5425, "write_kib": 1482},
-        "eval": {"source_sha256_16": "cfe308a8f566cbcf", "fetch_kib": 1110, "write_kib": 1.204e+04},
-        "nodes": {"source_sha256_16": "5fbb928bf73c535c", "fetch_kib": 7215, "write_kib": 1.654e+04},
-        "kv": {"source_sha256_16": "5fbb928bf73c535c", "fetch_kib": 4536, "write_kib": 1.423e+04},
-        "maxflow": {"source_sha256_16": "b931fad73ca81326", "fetch_kib": 1.674e+04, "write_kib": 768},
-        "best": {"source_sha256_16": "89724c3a7f9a387f", "fetch_kib": 18.1, "write_kib": 0.03125},
+        "setup": {"source_sha256_16": "900d7bafd42fa1cf", "fetch_kib": 70.55, "write_kib": 39.16},
+        "decode": {"source_sha256_16": "900d7bafd42fa1cf", "fetch_kib": 1700, "write_kib": 28860},
+        "scatter": {"source_sha256_16": "900d7bafd42fa1cf", "fetch_kib": 5421, "write_kib": 1487},
+        "eval": {"source_sha256_16": "900d7bafd42fa1cf", "fetch_kib": 1111, "write_kib": 12020},
+        "kv": {"source_sha256_16": "555313da00fbcfd3", "fetch_kib": 8451, "write_kib": 28430},
+        "maxflow": {"source_sha256_16": "2115c813c4485533", "fetch_kib": 11.95, "write_kib": 0.03125},
     },
     # workload 5, one chain round through hx_score_batch with the shared-groups hint
     # (profiles/chain_workload5.md): nodes is the settling nodes kernel, kv the link table,
     # maxflow the list-driven kernel, shared candidate 0's groups, best the split argmax
     5: {
-        "setup": {"source_sha256_16": "cfe308a8f566cbcf", "fetch_kib": 184.2, "write_kib": 516.1},
-        "shared": {"source_sha256_16": "cfe308a8f566cbcf", "fetch_kib": 179.9, "write_kib": 2},
-        "decode": {"source_sha256_16": "cfe308a8f566cbcf", "fetch_kib": 1.047e+04, "write_kib": 1.471e+05},
-        "scatter": {"source_sha256_16": "cfe308a8f566cbcf", "fetch_kib": 3.967e+04, "write_kib": 7565},
-        "eval": {"source_sha256_16": "cfe308a8f566cbcf", "fetch_kib": 9326, "write_kib": 3.268e+04},
-        "nodes": {"source_sha256_16": "5fbb928bf73c535c", "fetch_kib": 6.153e+04, "write_kib": 1536},
-        "kv": {"source_sha256_16": "5fbb928bf73c535c", "fetch_kib": 138.3, "write_kib": 68.03},
-        "maxflow": {"source_sha256_16": "b931fad73ca81326", "fetch_kib": 18.21, "write_kib": 0},
-        "best": {"source_sha256_16": "89724c3a7f9a387f", "fetch_kib": 297.3, "write_kib": 8.062},
+        "setup": {"source_sha256_16": "900d7bafd42fa1cf", "fetch_kib": 184.2, "write_kib": 516.1},
+        "shared": {"source_sha256_16": "900d7bafd42fa1cf", "fetch_kib": 166.9, "write_kib": 2},
+        "decode": {"source_sha256_16": "900d7bafd42fa1cf", "fetch_kib": 10470, "write_kib": 147500},
+        "scatter": {"source_sha256_16": "900d7bafd42fa1cf", "fetch_kib": 39700, "write_kib": 7562},
+        "eval": {"source_sha256_16": "900d7bafd42fa1cf", "fetch_kib": 9317, "write_kib": 32670},
+        "nodes": {"source_sha256_16": "555313da00fbcfd3", "fetch_kib": 61530, "write_kib": 1536},
+        "kv": {"source_sha256_16": "555313da00fbcfd3", "fetch_kib": 145.8, "write_kib": 68.03},
+        "maxflow": {"source_sha256_16": "2115c813c4485533", "fetch_kib": 18.64, "write_kib": 0},
+        "best": {"source_sha256_16": "4a046c3c30c2e032", "fetch_kib": 297.2, "write_kib": 8.062},
     },
 }
 # The guided-moves kernel at the refinement workload (profiles/refine_workload5.md), per launch of
 # 131,072 children, same scaling.
-MOVES_TRAFFIC = {"source_sha256_16": "2902f3b847ca3ebd", "children": 131072, "fetch_kib": 561.0,
+MOVES_TRAFFIC = {"source_sha256_16": "0fb2a44491a7dc6e", "children": 131072, "fetch_kib": 563.1,
                  "write_kib": 20990.0}
-# The partition kernel at workload 3 (profiles/partition_workload3.md), per launch of 16,384
+# The two partition kernels at workload 3 (profiles/partition_workload3.md), per call of 16,384
 # candidates, same scaling.
-PARTITION_TRAFFIC = {"source_sha256_16": "72b4245b3df4f290", "candidates": 16384, "fetch_kib": 1158.0,
+PARTITION_TRAFFIC = {"source_sha256_16": "492266fe45f9bbc2", "candidates": 16384, "fetch_kib": 494.4,
                      "write_kib": 6144.0}
 KERNEL_SOURCE = {"setup": "hx_cost.hip", "decode": "hx_cost.hip", "scatter": "hx_cost.hip", "eval": "hx_cost.hip",
                  "nodes": "hx_flownet.hip", "kv": "hx_flownet.hip", "maxflow": "hx_maxflow.hip",
@@ -612,9 +610,9 @@ def partition_main(args, torch, hx, I):
     hx.profile(False)
     kernel_us = {k: 1000.0 * v / c for k, (v, c) in prof.items() if c > 0}
     best = [int(x) for x in wsc.best.cpu().numpy()]
-    # the partition kernel against HBM: its algorithmic bytes are the candidates it writes (the
-    # weight table and order stay in cache); its time goes to Kernighan-Lin steps, each a
-    # workgroup-wide scan of the GPU pairs and two barriers, so the fraction is small
+    # the partition kernels against HBM: their algorithmic bytes are the candidates they write (the
+    # weight table and order stay in cache); the time goes to Kernighan-Lin steps, each an update
+    # of every pair's gain in registers and a maximum over them, so the fraction is small
     t_part = kernel_us["partition"] * 1e-6
     out_bytes = n * (prob.n_gpus + prob.max_groups)
     import hashlib
@@ -1042,6 +1040,8 @@ def main():
     dominant = max(kernel_us, key=kernel_us.get)
     hbm = hbm_bytes_per_step(prob, dims, n_p, n_d)
     kb = kernel_bytes(prob, n_p, n_d, settled_per_gpu=prob.granularity == 1 and prob.n_gpus <= 128)
+    if "nodes" not in kernel_us:  # replica networks: one kernel writes the nodes, KV rows and settled values
+        kb["kv"] += kb.pop("nodes") + 4 * prob.n_cand
     roof = roofline_for(dominant, kernel_us, prob, hbm, n_p, n_d, args.workload, kb)
     roof["measured_hbm_copy_gbs"] = measured_copy_gbs(torch)
 
