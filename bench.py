@@ -59,7 +59,7 @@ KERNEL_TRAFFIC = {
         "scatter": {"source_sha256_16": "900d7bafd42fa1cf", "fetch_kib": 5421, "write_kib": 1487},
         "eval": {"source_sha256_16": "900d7bafd42fa1cf", "fetch_kib": 1111, "write_kib": 12020},
         "kv": {"source_sha256_16": "555313da00fbcfd3", "fetch_kib": 8451, "write_kib": 28430},
-        "maxflow": {"source_sha256_16": "2115c813c4485533", "fetch_kib": 11.95, "write_kib": 0.03125},
+        "maxflow": {"source_sha256_16": "96b6285b66aa24bd", "fetch_kib": 11.95, "write_kib": 0.03125},
     },
     # workload 5, one chain round through hx_score_batch with the shared-groups hint
     # (profiles/chain_workload5.md): nodes is the settling nodes kernel, kv the link table,
@@ -72,7 +72,7 @@ KERNEL_TRAFFIC = {
         "eval": {"source_sha256_16": "900d7bafd42fa1cf", "fetch_kib": 9317, "write_kib": 32670},
         "nodes": {"source_sha256_16": "555313da00fbcfd3", "fetch_kib": 61530, "write_kib": 1536},
         "kv": {"source_sha256_16": "555313da00fbcfd3", "fetch_kib": 145.8, "write_kib": 68.03},
-        "maxflow": {"source_sha256_16": "2115c813c4485533", "fetch_kib": 18.64, "write_kib": 0},
+        "maxflow": {"source_sha256_16": "96b6285b66aa24bd", "fetch_kib": 18.64, "write_kib": 0},
         "best": {"source_sha256_16": "4a046c3c30c2e032", "fetch_kib": 297.2, "write_kib": 8.062},
     },
 }
@@ -84,6 +84,7 @@ MOVES_TRAFFIC = {"source_sha256_16": "0fb2a44491a7dc6e", "children": 131072, "fe
 # candidates, same scaling.
 PARTITION_TRAFFIC = {"source_sha256_16": "492266fe45f9bbc2", "candidates": 16384, "fetch_kib": 494.4,
                      "write_kib": 6144.0}
+TRAFFIC_CANDIDATES = {3: 65536, 5: 131072}  # the batches that the counters were taken on
 KERNEL_SOURCE = {"setup": "hx_cost.hip", "decode": "hx_cost.hip", "scatter": "hx_cost.hip", "eval": "hx_cost.hip",
                  "nodes": "hx_flownet.hip", "kv": "hx_flownet.hip", "maxflow": "hx_maxflow.hip",
                  "best": "hx_best.hip", "shared": "hx_cost.hip"}
@@ -241,7 +242,8 @@ def kernel_traffic(kernel: str, workload: int, prob=None):
     t = KERNEL_TRAFFIC.get(workload, {}).get(kernel)
     if t is None:
         return None
-    if prob is not None and (getattr(prob, "variant", 0) or getattr(prob, "classes", None) is not None):
+    if prob is not None and (getattr(prob, "variant", 0) or getattr(prob, "classes", None) is not None
+                             or prob.n_cand != TRAFFIC_CANDIDATES[workload]):
         return None
     src = os.path.join(ROOT, "paper_2502_07903_amd", "csrc", KERNEL_SOURCE[kernel])
     if hashlib.sha256(open(src, "rb").read()).hexdigest()[:16] != t["source_sha256_16"]:

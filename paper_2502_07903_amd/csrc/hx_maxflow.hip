@@ -142,7 +142,7 @@ __device__ __forceinline__ void global_relabel(const MfLayout& L, int l, int P, 
 // the same value (when only the value is asked for, it is left).
 // What bounds it: the latency of the dependent LDS accesses along a node's arcs; one wavefront needs
 // no barrier, and the networks in flight are bound by their LDS (four per CU at 128 GPUs).  4,096
-// networks of 16 to 64 nodes a side 1,836 -> 366 us, against a lane per node that scanned its whole row in
+// networks of 16 to 64 nodes a side 1,836 -> 350 us, against a lane per node that scanned its whole row in
 // every push and every sweep of a global relabel, with barriers between the phases (two wavefronts and
 // barriers on bit words: 492).
 template <int SEG>
@@ -1161,7 +1161,8 @@ __global__ void __launch_bounds__(SEG) maxflow_list_kernel(FlowNet f, int32_t* f
 // hx_score_batch with separate node, KV and max-flow kernels / with this kernel on 1,024 workgroups that
 // all took one ticket behind fences / now, 65,536 candidates: 5 networks listed of 4,096 (32 GPUs) 89 / 108 /
 // 73 us, 65,536 listed of 8 slots 182 / 261 / 183, 23,928 of 16 slots 119 / 171 / 98, 30,483 of 32 slots
-// 181 / 367 / 172, 64,102 of 16 slots that take push-relabel 657 / 1,408 / 727.
+// 181 / 367 / 169, 64,102 of 16 slots that take push-relabel 657 / 1,408 / 732 (33 us of it the network kernel's
+// walks): there a network's latency is what counts, and 32 wavefronts a CU had one each.
 constexpr int kFinishGrid = 6144;
 constexpr int kFinishParts = kNetTickets / 8;  // tickets of an XCD
 
